@@ -9,42 +9,11 @@ namespace laph {
 
 constexpr int kSetupBlock = 256;
 
-// 3x3 complex matrices in FP64 for the clover construction
-struct M3 {
-    cplx<double> m[9];
-};
-__device__ __forceinline__ M3 mmul(const M3 &a, const M3 &b) {
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            cplx<double> s = {0, 0};
-#pragma unroll
-            for (int k = 0; k < 3; ++k) cmac(s, a.m[i * 3 + k], b.m[k * 3 + j]);
-            c.m[i * 3 + j] = s;
-        }
-    return c;
-}
-__device__ __forceinline__ M3 adj(const M3 &a) {
-    M3 c;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) c.m[i * 3 + j] = conj(a.m[j * 3 + i]);
-    return c;
-}
-__device__ __forceinline__ M3 madd(const M3 &a, const M3 &b) {
-    M3 c;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) c.m[k] = a.m[k] + b.m[k];
-    return c;
-}
-
 // ---------------------------------------------------------------------------
 // gauge ingest
 // ---------------------------------------------------------------------------
-__global__ void gauge_pack_kernel(Geom g, const double2 *U, GaugePtrs gp, unsigned long long *maxdev) {
+__global__ __launch_bounds__(kSetupBlock) void gauge_pack_kernel(Geom g, const double2 *U, GaugePtrs gp,
+                                                                 unsigned long long *maxdev) {
     const long i = (long)blockIdx.x * kSetupBlock + threadIdx.x;
     const long vol = 2L * g.vh;
     if (i >= vol) return;
@@ -118,99 +87,246 @@ laph_status load_gauge(Ctx &c, const double *U) {
 // ---------------------------------------------------------------------------
 // clover term
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ M3 link64(const Geom &g, const GaugePtrs &gp, int x, int y, int z, int t, int mu) {
-    x = (x + g.lx) % g.lx;
-    y = (y + g.ly) % g.ly;
-    z = (z + g.lz) % g.lz;
-    t = (t + g.lt) % g.lt;
-    const int p = (x + y + z + t) & 1;
-    const int h = cb_index(g, x, y, z, t);
-    M3 u;
-    GaugeIO<F64>::load(gp, p, mu, g.vh, h, u.m);
-    return u;
+// A link read one row or column at a time.
+struct LinkRef {
+    const double2 *p;
+    size_t vh;
+    __device__ __forceinline__ cplx<double> at(int e) const {
+        const double2 v = p[e * vh];
+        return {v.x, v.y};
+    }
+    // column k and row k of the link, or of its adjoint
+    template <bool ADJ>
+    __device__ __forceinline__ void col(int k, cplx<double> (&c)[3]) const {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) c[i] = ADJ ? conj(at(3 * k + i)) : at(3 * i + k);
+    }
+    template <bool ADJ>
+    __device__ __forceinline__ void row(int k, cplx<double> (&c)[3]) const {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) c[i] = ADJ ? conj(at(3 * i + k)) : at(3 * k + i);
+    }
+};
+
+// the link in direction dir at the site x + dm mu + dn nu, dm, dn in {-1, 0, 1}
+template <int MU, int NU>
+__device__ __forceinline__ LinkRef link64(const Geom &g, const GaugePtrs &gp, const int (&x)[4], int dm, int dn,
+                                          int dir) {
+    const int ext[4] = {g.lx, g.ly, g.lz, g.lt};
+    int c[4] = {x[0], x[1], x[2], x[3]};
+    c[MU] += dm;
+    if (c[MU] < 0) c[MU] += ext[MU];
+    if (c[MU] == ext[MU]) c[MU] = 0;
+    c[NU] += dn;
+    if (c[NU] < 0) c[NU] += ext[NU];
+    if (c[NU] == ext[NU]) c[NU] = 0;
+    const int par = (c[0] + c[1] + c[2] + c[3]) & 1;
+    const char *base = par ? gp.f64[1][dir] : gp.f64[0][dir];
+    return {reinterpret_cast<const double2 *>(base) + cb_index(g, c[0], c[1], c[2], c[3]), (size_t)g.vh};
 }
 
-// F_munu(x) = (Q - Q^+)/8 minus its trace part, Q = sum of the four plaquettes at x
-__device__ M3 field_strength(const Geom &g, const GaugePtrs &gp, const int (&x)[4], int mu, int nu) {
-    auto at = [&](int dm, int dn, int dir) {
-        int c[4] = {x[0], x[1], x[2], x[3]};
-        c[mu] += dm;
-        c[nu] += dn;
-        return link64(g, gp, c[0], c[1], c[2], c[3], dir);
-    };
-    M3 q;
-    // x -> x+mu -> x+mu+nu -> x+nu -> x
-    q = mmul(mmul(at(0, 0, mu), at(1, 0, nu)), mmul(adj(at(0, 1, mu)), adj(at(0, 0, nu))));
-    // x -> x+nu -> x+nu-mu -> x-mu -> x
-    q = madd(q, mmul(mmul(at(0, 0, nu), adj(at(-1, 1, mu))), mmul(adj(at(-1, 0, nu)), at(-1, 0, mu))));
-    // x -> x-mu -> x-mu-nu -> x-nu -> x
-    q = madd(q, mmul(mmul(adj(at(-1, 0, mu)), adj(at(-1, -1, nu))), mmul(at(-1, -1, mu), at(0, -1, nu))));
-    // x -> x-nu -> x-nu+mu -> x+mu -> x
-    q = madd(q, mmul(mmul(adj(at(0, -1, nu)), at(0, -1, mu)), mmul(at(1, -1, nu), adj(at(0, 0, mu)))));
-    M3 f;
-    cplx<double> tr = {0, 0};
+// s += a b (fused multiply-add chain), SUB: s -= a b
+template <bool SUB>
+__device__ __forceinline__ void zmac(cplx<double> &s, cplx<double> a, cplx<double> b) {
+    const double re = SUB ? -a.re : a.re, im = SUB ? -a.im : a.im;
+    s.re = ffma(re, b.re, s.re);
+    s.re = ffma(-im, b.im, s.re);
+    s.im = ffma(re, b.im, s.im);
+    s.im = ffma(im, b.re, s.im);
+}
+
+// s += op(A) op(B) op(C) (SUB: -=), as sums of outer products so that at most a column and a
+// row of a link are live beside the two 3x3 accumulators
+template <bool ADJ_A, bool ADJ_B, bool ADJ_C, bool SUB>
+__device__ __forceinline__ void staple(cplx<double> (&s)[9], LinkRef A, LinkRef B, LinkRef C) {
+    cplx<double> t[9], u[3], v[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int e = 0; e < 9; ++e) t[e] = {0.0, 0.0};
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            f.m[i * 3 + j] = 0.125 * (q.m[i * 3 + j] - conj(q.m[j * 3 + i]));
-            if (i == j) tr = tr + f.m[i * 3 + j];
+    for (int k = 0; k < 3; ++k) {
+        A.col<ADJ_A>(k, u);
+        B.row<ADJ_B>(k, v);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) zmac<false>(t[3 * i + j], u[i], v[j]);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        C.row<ADJ_C>(k, v);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) zmac<SUB>(s[3 * i + j], t[3 * i + k], v[j]);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // later links are not loaded early (registers)
+}
+
+// An anti-Hermitian 3x3 matrix: i d[k] on the diagonal, o = entries (1,0), (2,0), (2,1).
+struct AH3 {
+    double d[3];
+    cplx<double> o[3];
+};
+// f += u v - (u v)^+ for a column u and a row v
+__device__ __forceinline__ void ah_mac(AH3 &f, const cplx<double> (&u)[3], const cplx<double> (&v)[3]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        f.d[k] = ffma(2.0 * u[k].re, v[k].im, f.d[k]);
+        f.d[k] = ffma(2.0 * u[k].im, v[k].re, f.d[k]);
+    }
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        const int i = e == 0 ? 1 : 2, j = e == 2 ? 1 : 0;
+        zmac<false>(f.o[e], u[i], v[j]);
+        zmac<true>(f.o[e], conj(u[j]), conj(v[i]));
+    }
+}
+
+// F_munu(x) = (Q - Q^+)/8 minus its trace part, Q = sum of the four plaquettes at x.  Q - Q^+
+// does not change when a plaquette is replaced by minus its adjoint, so the two plaquettes
+// that begin with U_mu(x), and the two that end with U_mu(x - mu), share that factor:
+//   Q - Q^+ = W - W^+,  W = U_mu(x) (S1 - S4) + (S2 - S3) U_mu(x - mu)
+// (ten 3x3 products instead of twelve).
+template <int MU, int NU>
+__device__ __forceinline__ AH3 field_strength(const Geom &g, const GaugePtrs &gp, const int (&x)[4]) {
+    auto at = [&](int dm, int dn, int dir) { return link64<MU, NU>(g, gp, x, dm, dn, dir); };
+    AH3 f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        f.d[k] = 0.0;
+        f.o[k] = {0.0, 0.0};
+    }
+    cplx<double> s[9], u[3];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) s[e] = {0.0, 0.0};
+        if (half == 0) {
+            // S1 = U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+,  S4 = U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu)
+            staple<false, true, true, false>(s, at(1, 0, NU), at(0, 1, MU), at(0, 0, NU));
+            staple<true, true, false, true>(s, at(1, -1, NU), at(0, -1, MU), at(0, -1, NU));
+            const LinkRef U = at(0, 0, MU);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const cplx<double> r[3] = {s[3 * k], s[3 * k + 1], s[3 * k + 2]};
+                U.col<false>(k, u);
+                ah_mac(f, u, r);
+            }
+        } else {
+            // S2 = U_nu(x) U_mu(x-mu+nu)^+ U_nu(x-mu)^+,  S3 = U_nu(x-nu)^+ U_mu(x-mu-nu)^+ U_nu(x-mu-nu)
+            staple<false, true, true, false>(s, at(0, 0, NU), at(-1, 1, MU), at(-1, 0, NU));
+            staple<true, true, false, true>(s, at(0, -1, NU), at(-1, -1, MU), at(-1, -1, NU));
+            const LinkRef U = at(-1, 0, MU);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const cplx<double> c[3] = {s[k], s[3 + k], s[6 + k]};
+                U.row<false>(k, u);
+                ah_mac(f, c, u);
+            }
         }
+    }
+    const double tr = (f.d[0] + f.d[1] + f.d[2]) / 3.0;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) f.m[i * 4] = f.m[i * 4] - (1.0 / 3.0) * tr;
+    for (int k = 0; k < 3; ++k) {
+        f.d[k] = 0.125 * (f.d[k] - tr);
+        f.o[k] = 0.125 * f.o[k];
+    }
     return f;
+}
+
+// (i csw / 2) (a + s b), a Hermitian matrix: real diagonal, entries (1,0), (2,0), (2,1)
+struct H3 {
+    double d[3];
+    cplx<double> o[3];
+};
+__device__ __forceinline__ H3 half_i(double csw, const AH3 &a, double s, const AH3 &b) {
+    const double f = 0.5 * csw;
+    H3 h;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) h.d[k] = -f * ffma(s, b.d[k], a.d[k]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        h.o[k] = {-f * ffma(s, b.o[k].im, a.o[k].im), f * ffma(s, b.o[k].re, a.o[k].re)};
+    return h;
+}
+// entry (a, b) of an H3
+__device__ __forceinline__ cplx<double> h3_at(const H3 &h, int a, int b) {
+    if (a == b) return {h.d[a], 0.0};
+    const int hi = a > b ? a : b, lo = a > b ? b : a;
+    const cplx<double> e = hi == 1 ? h.o[0] : h.o[1 + lo];
+    return a > b ? e : conj(e);
 }
 
 // Packed Hermitian clover term per site and chiral block (without 4 + m0):
 // in this gamma basis sigma_munu is block diagonal; on spins {0,1} (block 0)
 //   sum sigma (x) F = sx (x) (Fyz - Fxt) + sy (x) (Fxz + Fyt) + sz (x) (Fxy - Fzt)
 // and on spins {2,3} (block 1) the signs of the time planes flip, with
-// sx, sy, sz the Pauli matrices.  The block is (i/2) c_sw times that sum.
-__global__ void clover_build_kernel(Geom g, GaugePtrs gp, double csw, char *term0, char *term1) {
-    const int h = blockIdx.x * kSetupBlock + threadIdx.x;
+// sx, sy, sz the Pauli matrices.  The block is (i/2) c_sw times that sum,
+// [[Gz, Gx - i Gy], [Gx + i Gy, -Gz]] with index 3 s' + a.
+//
+// One wave per plane on 64 sites: the six field strengths (9 reals each) meet in LDS and
+// every wave assembles the entries of its plane's partners.  Bound by the gather of the
+// links (60 per site, 8.6 KB, through the caches): the waves of a block read the same
+// links at about the same time, and products taken as outer products keep a wave small.
+// 32^3 x 64: 2.4 ms.  One thread with all six planes as full matrices, under the default
+// 1024-thread register budget, spilled 1208 registers and took 6.56 ms; the same at 256
+// registers 3.63 ms.  Walking the blocks XCD by XCD, or both parities together, changes
+// nothing.
+constexpr int kCloverSites = 64;
+
+__global__ __launch_bounds__(6 * 64) __attribute__((amdgpu_waves_per_eu(3))) void clover_build_kernel(
+    Geom g, GaugePtrs gp, double csw, char *term0, char *term1) {
+    __shared__ AH3 F[6][kCloverSites];   // xy, zt, yz, xt, xz, yt
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int h = blockIdx.x * kCloverSites + lane;
     const int p = blockIdx.y;
-    if (h >= g.vh) return;
+    const bool valid = h < g.vh;
     int x[4];
-    site_coords(g, p, h, x[0], x[1], x[2], x[3]);
-    M3 Fxy = field_strength(g, gp, x, 0, 1), Fxz = field_strength(g, gp, x, 0, 2);
-    M3 Fyz = field_strength(g, gp, x, 1, 2), Fxt = field_strength(g, gp, x, 0, 3);
-    M3 Fyt = field_strength(g, gp, x, 1, 3), Fzt = field_strength(g, gp, x, 2, 3);
-    double2 *dst = reinterpret_cast<double2 *>(p == 0 ? term0 : term1);
-    for (int blk = 0; blk < 2; ++blk) {
-        const double sgn = blk == 0 ? -1.0 : 1.0;
-        cplx<double> Gx[9], Gy[9], Gz[9];
-        const cplx<double> ihalf = {0.0, 0.5 * csw};
-        for (int k = 0; k < 9; ++k) {
-            Gx[k] = ihalf * (Fyz.m[k] + sgn * Fxt.m[k]);
-            Gy[k] = ihalf * (Fxz.m[k] - sgn * Fyt.m[k]);
-            Gz[k] = ihalf * (Fxy.m[k] + sgn * Fzt.m[k]);
+    site_coords(g, p, valid ? h : g.vh - 1, x[0], x[1], x[2], x[3]);
+    switch (wave) {
+        case 0: F[0][lane] = field_strength<0, 1>(g, gp, x); break;
+        case 1: F[1][lane] = field_strength<2, 3>(g, gp, x); break;
+        case 2: F[2][lane] = field_strength<1, 2>(g, gp, x); break;
+        case 3: F[3][lane] = field_strength<0, 3>(g, gp, x); break;
+        case 4: F[4][lane] = field_strength<0, 2>(g, gp, x); break;
+        default: F[5][lane] = field_strength<1, 3>(g, gp, x); break;
+    }
+    __syncthreads();
+    if (!valid) return;
+    const size_t vh = g.vh;
+    const int blk = wave & 1, part = wave >> 1;
+    const double sgn = blk == 0 ? -1.0 : 1.0;
+    double2 *d = reinterpret_cast<double2 *>(p == 0 ? term0 : term1) + blk * 18 * vh + h;
+    if (part == 0) {
+        // the diagonal, then the entries of equal spin: packed index 3 + (i (i - 1) / 2 + j)
+        const H3 z = half_i(csw, F[0][lane], sgn, F[1][lane]);
+        d[0] = make_double2(z.d[0], z.d[1]);
+        d[vh] = make_double2(z.d[2], -z.d[0]);
+        d[2 * vh] = make_double2(-z.d[1], -z.d[2]);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            const int i = e == 0 ? 1 : 2, j = e == 2 ? 1 : 0, i1 = i + 3, j1 = j + 3;
+            d[(3 + i * (i - 1) / 2 + j) * vh] = make_double2(z.o[e].re, z.o[e].im);
+            d[(3 + i1 * (i1 - 1) / 2 + j1) * vh] = make_double2(-z.o[e].re, -z.o[e].im);
         }
-        // 6x6 = [[Gz, Gx - i Gy], [Gx + i Gy, -Gz]], index 3 s' + a
-        double pk[36];
-        auto entry = [&](int i, int j) -> cplx<double> {
-            const int si = i / 3, a = i % 3, sj = j / 3, b = j % 3;
-            const int k = a * 3 + b;
-            if (si == 0 && sj == 0) return Gz[k];
-            if (si == 1 && sj == 1) return cplx<double>{-Gz[k].re, -Gz[k].im};
-            if (si == 1 && sj == 0) return Gx[k] + mul_i(Gy[k]);
-            return Gx[k] - mul_i(Gy[k]);
-        };
-        for (int i = 0; i < 6; ++i) pk[i] = entry(i, i).re;
-        int k = 0;
-        for (int i = 1; i < 6; ++i)
-            for (int j = 0; j < i; ++j) {
-                cplx<double> e = entry(i, j);
-                pk[6 + 2 * k] = e.re;
-                pk[7 + 2 * k] = e.im;
-                ++k;
+    } else {
+        // Gx + i Gy: rows 0 and 1 (first half), row 2 (second half)
+        const H3 gx = half_i(csw, F[2][lane], sgn, F[3][lane]), gy = half_i(csw, F[4][lane], -sgn, F[5][lane]);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if ((a == 2) != (part == 2)) continue;
+            const int i = a + 3;
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const cplx<double> e = h3_at(gx, a, b) + mul_i(h3_at(gy, a, b));
+                d[(3 + i * (i - 1) / 2 + b) * vh] = make_double2(e.re, e.im);
             }
-        double2 *d = dst + (size_t)blk * 18 * g.vh;
-        for (int q = 0; q < 18; ++q) d[(size_t)q * g.vh + h] = make_double2(pk[2 * q], pk[2 * q + 1]);
+        }
     }
 }
 
 // Inverse of (term + shift) per site and block by Cholesky: A = L L^+, A^-1 = W^+ W, W = L^-1.
-__global__ void clover_invert_kernel(int vh, const char *term, double shift, char *inv64, char *inv32, int *bad) {
+__global__ __launch_bounds__(kSetupBlock) void clover_invert_kernel(int vh, const char *term, double shift, char *inv64, char *inv32, int *bad) {
     const int h = blockIdx.x * kSetupBlock + threadIdx.x;
     const int blk = blockIdx.y;
     if (h >= vh) return;
@@ -288,8 +404,8 @@ __global__ void clover_invert_kernel(int vh, const char *term, double shift, cha
 laph_status build_clover(Ctx &c, double csw, int n_mass, const double *m0) {
     char *t0 = c.state + c.off_clov;
     char *t1 = t0 + c.sz_cl64_par;
-    dim3 grid((c.g.vh + kSetupBlock - 1) / kSetupBlock, 2);
-    hipLaunchKernelGGL(clover_build_kernel, grid, dim3(kSetupBlock), 0, c.stream, c.g, c.gp, csw, t0, t1);
+    dim3 grid((c.g.vh + kCloverSites - 1) / kCloverSites, 2);
+    hipLaunchKernelGGL(clover_build_kernel, grid, dim3(6 * 64), 0, c.stream, c.g, c.gp, csw, t0, t1);
     LAPH_TRY(check_launch("clover_build_kernel"));
     double *diag = c.mass_diag();
     int *d_bad = c.bad_flag();
