@@ -61,17 +61,26 @@ __device__ __forceinline__ cplx<R> c_of(double2 z) {
     return {R(z.x), R(z.y)};
 }
 
-// p = r + beta (p - omega v);  beta == 0 means p = r (fresh start: p, v not read)
+// first site of this block; grids of windowed updates walk the blocks the window touches
+__device__ __forceinline__ int first_site(const BlasArgs &A) {
+    int b = A.sb_first + blockIdx.x;
+    if (b >= A.nsb) b -= A.nsb;
+    return b * kB;
+}
+
+// p = r + beta (p - omega v);  beta == 0 means p = r (fresh start: p, v not read).
+// Sites outside A.win are not touched; outside A.win_pv p and v are zero and not read.
 template <class P>
 __global__ __launch_bounds__(kB) void p_update_kernel(BlasArgs A) {
     using R = typename P::real;
-    const int h = blockIdx.x * kB + threadIdx.x;
-    if (h >= A.vh) return;
+    const int h = first_site(A) + threadIdx.x;
+    if (h >= A.vh || !in_window(A.win, h, A.vh)) return;
+    const bool zero_pv = !in_window(A.win_pv, h, A.vh);
     LAPH_FOR_SLOTS(A, kModeActive, s) {
         const double2 beta = A.st[s].beta;
         cplx<R> r[12];
         SpinorIO<P>::load(A.r.at(s), A.vh, h, r);
-        if (beta.x == 0.0 && beta.y == 0.0) {
+        if (zero_pv || (beta.x == 0.0 && beta.y == 0.0)) {
             SpinorIO<P>::store(A.p.at(s), A.vh, h, r);
             continue;
         }
@@ -89,8 +98,8 @@ __global__ __launch_bounds__(kB) void p_update_kernel(BlasArgs A) {
 template <class P>
 __global__ __launch_bounds__(kB) void s_update_kernel(BlasArgs A) {
     using R = typename P::real;
-    const int h = blockIdx.x * kB + threadIdx.x;
-    if (h >= A.vh) return;
+    const int h = first_site(A) + threadIdx.x;
+    if (h >= A.vh || !in_window(A.win, h, A.vh)) return;
     LAPH_FOR_SLOTS(A, kModeActive, s) {
         const cplx<R> al = c_of<R>(A.st[s].alpha);
         cplx<R> r[12], v[12];
@@ -103,15 +112,26 @@ __global__ __launch_bounds__(kB) void s_update_kernel(BlasArgs A) {
 }
 
 // x_lo += alpha p + omega s (x_lo = ... after a fold or at the start);  r = s - omega t;
-// partials <r^, r>, |r|^2
+// partials <r^, r>, |r|^2.  Outside A.win p, s and t are zero: nothing to do there, except
+// that an x_lo marked zero becomes zero in memory.  r^ is not read where it is zero.
 template <class P, class PX>
 __global__ __launch_bounds__(kB) void xr_update_kernel(BlasArgs A) {
     using R = typename P::real;
     using RX = typename PX::real;
-    const int h = blockIdx.x * kB + threadIdx.x;
+    const int h0 = blockIdx.x * kB, h = h0 + threadIdx.x;
+    const bool outside = block_outside(A.win, h0, min(kB, A.vh - h0), A.vh);   // uniform
+    const bool live = h < A.vh && in_window(A.win, h, A.vh);
+    const bool rh_zero = block_outside(A.win_rh, h0, min(kB, A.vh - h0), A.vh) && *A.rh_full == 0;
     LAPH_FOR_SLOTS(A, kModeActive, s) {
+        if (!live && h < A.vh && A.st[s].xlo_zero) {
+            cplx<RX> x[12];
+#pragma unroll
+            for (int c = 0; c < 12; ++c) x[c] = {RX(0), RX(0)};
+            SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
+        }
+        if (outside) continue;
         double part[3] = {0, 0, 0};
-        if (h < A.vh) {
+        if (live) {
             const cplx<R> al = c_of<R>(A.st[s].alpha), om = c_of<R>(A.st[s].omega);
             cplx<R> p[12], r[12], t[12], rh[12];
             cplx<RX> x[12];
@@ -132,13 +152,14 @@ __global__ __launch_bounds__(kB) void xr_update_kernel(BlasArgs A) {
             }
             SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
             SpinorIO<P>::store(A.r.at(s), A.vh, h, r);
-            SpinorIO<P>::load(A.rh.at(s), A.vh, h, rh);
             cplx<R> d = {R(0), R(0)};
             R n2 = R(0);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                cmac_conj(d, rh[c], r[c]);
-                n2 += r[c].re * r[c].re + r[c].im * r[c].im;
+            for (int c = 0; c < 12; ++c) n2 += r[c].re * r[c].re + r[c].im * r[c].im;
+            if (!rh_zero) {
+                SpinorIO<P>::load(A.rh.at(s), A.vh, h, rh);
+#pragma unroll
+                for (int c = 0; c < 12; ++c) cmac_conj(d, rh[c], r[c]);
             }
             part[0] = d.re;
             part[1] = d.im;
@@ -167,13 +188,16 @@ __global__ __launch_bounds__(kB) void accumulate_kernel(BlasArgs A, int mode) {
     }
 }
 
-// r = lo(r64); restart (flag 2) or init: r^ = r (the init finalize marks x_lo zero).
+// r = lo(r64); restart (flag 2) or init: r^ = r (the init finalize marks x_lo zero).  init 1: r
+// lives on the source's window, 2: on the whole lattice.
 // partials <r^, r>, |r|^2
 template <class P, class PX>
 __global__ __launch_bounds__(kB) void lower_kernel(BlasArgs A, int mode, int init) {
     using R = typename P::real;
     const int h = blockIdx.x * kB + threadIdx.x;
     LAPH_FOR_SLOTS(A, mode, s) {
+        // a restart replaces r^: it is no longer confined to the source's window
+        if ((init || A.st[s].flag == 2) && blockIdx.x == 0 && threadIdx.x == 0) *A.rh_full = init != 1;
         double part[3] = {0, 0, 0};
         if (h < A.vh) {
             cplx<double> y[12];
@@ -296,14 +320,19 @@ __global__ __launch_bounds__(kB) void flag_tiles_kernel(FlagArgs A) {
 // Eight independent loads in flight per lane: the partials were just written by
 // workgroups on every XCD, and a loop that waits for each load in turn spends ~0.1 ms
 // of latency per slot and quantity.  The summation order is still fixed.
-__device__ __forceinline__ double wave_sum_partials(const double *p, int nsb) {
+// A windowed producer wrote only A.count blocks from A.first on (cyclic).
+__device__ __forceinline__ double wave_sum_partials(const double *p, const FinArgs &A) {
     double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    auto at = [&](int i) {
+        const int b = A.first + i;
+        return p[b < A.nsb ? b : b - A.nsb];
+    };
     int i = threadIdx.x;
-    for (; i + 7 * 64 < nsb; i += 8 * 64) {
+    for (; i + 7 * 64 < A.count; i += 8 * 64) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) a[k] += p[i + 64 * k];
+        for (int k = 0; k < 8; ++k) a[k] += at(i + 64 * k);
     }
-    for (; i < nsb; i += 64) a[0] += p[i];
+    for (; i < A.count; i += 64) a[0] += at(i);
     double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
@@ -330,7 +359,7 @@ __global__ void finalize_kernel(FinArgs A, int what) {
     switch (what) {
         case kFinAlpha: {  // sigma = <r^, v>; alpha = rho / sigma
             if (!active) return;
-            const double2 sig = make_double2(wave_sum_partials(P, A.nsb), wave_sum_partials(P + A.pstride, A.nsb));
+            const double2 sig = make_double2(wave_sum_partials(P, A), wave_sum_partials(P + A.pstride, A));
             if (threadIdx.x) return;
             if (!finite2(sig) || cabs2(sig) <= 1e-300 * (cabs2(st.rho) + 1e-300) || cabs2(sig) == 0.0) {
                 st.alpha = make_double2(0, 0);
@@ -342,8 +371,8 @@ __global__ void finalize_kernel(FinArgs A, int what) {
         }
         case kFinOmega: {  // omega = <t, s> / |t|^2
             if (!active) return;
-            const double2 ts = make_double2(wave_sum_partials(P, A.nsb), wave_sum_partials(P + A.pstride, A.nsb));
-            const double tt = wave_sum_partials(P + 2 * A.pstride, A.nsb);
+            const double2 ts = make_double2(wave_sum_partials(P, A), wave_sum_partials(P + A.pstride, A));
+            const double tt = wave_sum_partials(P + 2 * A.pstride, A);
             if (threadIdx.x) return;
             if (!(tt > 0) || !isfinite(tt) || !finite2(ts)) {
                 st.omega = make_double2(0, 0);
@@ -355,8 +384,8 @@ __global__ void finalize_kernel(FinArgs A, int what) {
         }
         case kFinRho: {  // rho_new = <r^, r>, r2 = |r|^2; beta; decide on a reliable update
             if (!active) return;
-            const double2 rn = make_double2(wave_sum_partials(P, A.nsb), wave_sum_partials(P + A.pstride, A.nsb));
-            const double r2 = wave_sum_partials(P + 2 * A.pstride, A.nsb);
+            const double2 rn = make_double2(wave_sum_partials(P, A), wave_sum_partials(P + A.pstride, A));
+            const double r2 = wave_sum_partials(P + 2 * A.pstride, A);
             if (threadIdx.x) return;
             st.iters += 1;
             st.r2 = r2;
@@ -376,7 +405,7 @@ __global__ void finalize_kernel(FinArgs A, int what) {
         }
         case kFinUpdate: {  // r2_upd = |b_hat - M x64|^2 after a reliable update
             if (!(active && st.flag != 0)) return;
-            const double r2 = wave_sum_partials(P, A.nsb);
+            const double r2 = wave_sum_partials(P, A);
             if (threadIdx.x) return;
             st.updates += 1;
             st.r2_upd = r2;
@@ -397,8 +426,8 @@ __global__ void finalize_kernel(FinArgs A, int what) {
         case kFinInit: {  // first residual of a solve
             const bool init = what == kFinInit;
             if (!(active && (init || st.flag != 0))) return;
-            const double2 rn = make_double2(wave_sum_partials(P, A.nsb), wave_sum_partials(P + A.pstride, A.nsb));
-            const double r2 = wave_sum_partials(P + 2 * A.pstride, A.nsb);
+            const double2 rn = make_double2(wave_sum_partials(P, A), wave_sum_partials(P + A.pstride, A));
+            const double r2 = wave_sum_partials(P + 2 * A.pstride, A);
             if (threadIdx.x) return;
             st.r2 = r2;
             if (init || st.flag == 2) {
@@ -415,7 +444,7 @@ __global__ void finalize_kernel(FinArgs A, int what) {
             return;
         }
         case kFinBnorm: {  // |B|^2 of the full-lattice source; zero or non-finite sources end here
-            const double b2 = wave_sum_partials(P, A.nsb);
+            const double b2 = wave_sum_partials(P, A);
             if (threadIdx.x) return;
             st.bnorm2 = b2;
             if (!isfinite(b2)) st.status = LAPH_RHS_NONFINITE;
@@ -423,7 +452,7 @@ __global__ void finalize_kernel(FinArgs A, int what) {
         }
         case kFinR64: {  // |r64|^2 at the start of a solve pass
             if (!active) return;
-            const double r2 = wave_sum_partials(P, A.nsb);
+            const double r2 = wave_sum_partials(P, A);
             if (threadIdx.x) return;
             st.r2_upd = r2;
             if (!isfinite(r2)) st.status = LAPH_RHS_NONFINITE;
@@ -431,7 +460,7 @@ __global__ void finalize_kernel(FinArgs A, int what) {
             return;
         }
         case kFinTrueRes: {  // accumulate |B - D X|^2 (called for the even and the odd part)
-            const double r2 = wave_sum_partials(P, A.nsb);
+            const double r2 = wave_sum_partials(P, A);
             if (threadIdx.x) return;
             st.true_res2 += r2;
             return;
@@ -450,16 +479,18 @@ static laph_status dispatch_prec(int prec, F &&f) {
 }
 
 laph_status blas_p_update(const Ctx &c, const BlasArgs &a, int prec) {
-    dim3 grid(a.nsb, a.nlist_max);
+    BlasArgs w = a;
+    dim3 grid(window_blocks(a.win, kB, a.nsb, a.vh, &w.sb_first), a.nlist_max);
     return dispatch_prec(prec, [&](auto P, auto) {
-        hipLaunchKernelGGL(p_update_kernel<decltype(P)>, grid, dim3(kB), 0, c.stream, a);
+        hipLaunchKernelGGL(p_update_kernel<decltype(P)>, grid, dim3(kB), 0, c.stream, w);
         return check_launch("p_update_kernel");
     });
 }
 laph_status blas_s_update(const Ctx &c, const BlasArgs &a, int prec) {
-    dim3 grid(a.nsb, a.nlist_max);
+    BlasArgs w = a;
+    dim3 grid(window_blocks(a.win, kB, a.nsb, a.vh, &w.sb_first), a.nlist_max);
     return dispatch_prec(prec, [&](auto P, auto) {
-        hipLaunchKernelGGL(s_update_kernel<decltype(P)>, grid, dim3(kB), 0, c.stream, a);
+        hipLaunchKernelGGL(s_update_kernel<decltype(P)>, grid, dim3(kB), 0, c.stream, w);
         return check_launch("s_update_kernel");
     });
 }

@@ -241,14 +241,8 @@ laph_status laph_attach_state(laph_ctx h, void *dev, size_t bytes) try {
     if (bytes < c.state_size) return set_error(LAPH_ERR_WORKSPACE, "state buffer too small: %zu < %zu", bytes, c.state_size);
     if (reinterpret_cast<uintptr_t>(dev) % 256) return set_error(LAPH_ERR_INVALID, "state buffer must be 256-byte aligned");
     c.state = reinterpret_cast<char *>(dev);
-    for (int p = 0; p < 2; ++p)
-        for (int mu = 0; mu < 4; ++mu) {
-            const int i = p * 4 + mu;
-            c.gp.f64[p][mu] = c.state + c.off_g64 + i * c.sz_g64_pm;
-            c.gp.f32[p][mu] = c.state + c.off_g32 + i * c.sz_g32_pm;
-            c.gp.f16a[p][mu] = c.state + c.off_g16a + i * c.sz_g16a_pm;
-            c.gp.f16b[p][mu] = c.state + c.off_g16b + i * c.sz_g16b_pm;
-        }
+    c.gp = GaugePtrs{c.state + c.off_g64, c.state + c.off_g32, c.state + c.off_g16a, c.state + c.off_g16b,
+                     c.sz_g64_pm, c.sz_g32_pm, c.sz_g16a_pm, c.sz_g16b_pm};
     std::vector<int> ident(3 * kIdentMax);
     for (int i = 0; i < kIdentMax; ++i) {
         ident[i] = i;

@@ -57,6 +57,14 @@ laph_status launch_stage(const Ctx &c, const StageSpec &s) {
     lds_block_tiles(c, s, a);
     a.dispatch_order = s.form == kFormLds ? 1 : 0;
     a.win = s.win;
+    a.win_w = s.win_w;
+    a.w_full = s.w_full;
+    // the site blocks the window touches, in whole rows of block tiles (the tiled order has the
+    // timeslice tiles outermost)
+    const int sites = s.form == kFormLds ? kLdsSites : kBlock;
+    const int row = a.tz ? a.tt * c.g.lz * a.nyb : 1;
+    a.nsb_win = row * window_blocks(s.win, sites * row, a.nsb / row, c.g.vh, &a.sb_first);
+    a.sb_first *= row;
     a.clover_term = (s.red == 4 || s.red == 5) ? c.clover_term(s.out_parity) : nullptr;
     a.diag = c.mass_diag();
     a.flag_filter = s.flagged;
@@ -65,8 +73,7 @@ laph_status launch_stage(const Ctx &c, const StageSpec &s) {
     a.partials = s.partials;
     if (a.ntiles_max <= 0) return LAPH_OK;
     if (s.red && s.pstride < a.nsb) return set_error(LAPH_ERR_INVALID, "partial-sum stride too small");
-    // a skipped site block would leave its partial sums unwritten
-    if (s.red && s.win.n > 0) return set_error(LAPH_ERR_INVALID, "site window on a reducing stage");
+    if (s.red == 1 && s.win_w.n > 0 && !s.w_full) return set_error(LAPH_ERR_INVALID, "window of w without its flag");
     bool ok = false;
     if (s.form == kFormLds) {
         if (s.prec == LAPH_F64)

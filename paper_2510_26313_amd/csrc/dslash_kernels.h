@@ -20,15 +20,16 @@
 
 namespace laph {
 
-constexpr int kBlock = 256;
-
-// Register budget of the stencil kernels: ask for at least this many waves per
-// SIMD so the compiler keeps the kernel under 512 / N VGPRs (memory latency is
-// hidden by occupancy; the accumulators of a 4-RHS tile still fit).
-#ifndef LAPH_STAGE_WAVES
-#define LAPH_STAGE_WAVES 1
-#endif
-#define LAPH_STAGE_OCCUPANCY __attribute__((amdgpu_waves_per_eu(LAPH_STAGE_WAVES)))
+// Waves per SIMD the register form's kernels are compiled for: its single-RHS FP32 / FP16N
+// tiles need 120-134 registers and are held at the 128 that 4 waves leave; the larger tiles
+// keep their accumulators in up to 512 registers.
+template <class P, int NR>
+constexpr int kStageWaves = NR == 1 && sizeof(typename P::real) == 4 ? 4 : 1;
+// The FP64 single-RHS tile serves launches of about one workgroup per CU: scheduled for at
+// most 2 waves per SIMD it keeps more of the gather in flight (16^3 x 32, the stage with
+// <r^, v>: 30.3 us; scheduled for 3 waves 32.5 us).
+template <class P, int NR>
+constexpr int kStageWavesMax = NR == 1 && sizeof(typename P::real) == 8 ? 2 : 8;
 
 struct StageArgs {
     Geom g;
@@ -55,6 +56,11 @@ struct StageArgs {
     int nyb, tz, tt;
     int dispatch_order;   // 1: items in dispatch order (see stage_item_range); 0: per-XCD ranges
     SiteWindow win;       // output sites computed; the others are neither read nor written
+    // LDS form: the launch walks nsb_win site blocks from sb_first (cyclic, in the tiled order); the
+    // register form, which serves a few RHS, skips the blocks outside the window
+    int nsb_win, sb_first;
+    SiteWindow win_w;        // reduction 1 (LDS form): w is zero outside (not read), unless *w_full
+    const int *w_full;
     // reductions 4 and 5 (FP64 LDS form): the clover term of the output parity and the
     // per-mass diagonal 4 + m0 (|v - A out|^2; a y + b H in - A y2)
     const char *clover_term;
@@ -100,6 +106,10 @@ __device__ __forceinline__ void stage_item(int w, int site_major, int nsb, int n
         sb = w / ntiles;
         tile = w - sb * ntiles;
     }
+}
+// the w operand of reduction 1 is zero on this block of sites
+__device__ __forceinline__ bool w_is_zero(const StageArgs &A, int h0, int cnt) {
+    return block_outside(A.win_w, h0, min(cnt, A.g.vh - h0), A.g.vh) && *A.w_full == 0;
 }
 // Physical site block of the L-th block in the tiled order: within a tile the y
 // blocks run fastest, then tz z-planes, then tt timeslices; tiles go in z, then t.
@@ -486,7 +496,8 @@ __device__ __forceinline__ void stage_body(const StageArgs &A, int sb, int tile)
 }
 
 template <class P, int NR, bool DAG, bool CLOVER, bool PRE, int POST, int RED, bool FLAGGED>
-__global__ __launch_bounds__(kBlock) LAPH_STAGE_OCCUPANCY void stage_kernel(StageArgs A) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStageWaves<P, NR>, kStageWavesMax<P, NR>))) void stage_kernel(
+    StageArgs A) {
     const int nt = *A.ntiles;
     int first, end, step;
     stage_item_range(nt * A.nsb, A.dispatch_order, first, end, step);

@@ -17,8 +17,6 @@
 
 namespace laph {
 
-constexpr int kLdsSites = 64;
-
 // One hop for one RHS: neighbour index and link (already L or L^dagger, times the
 // boundary sign) come from LDS; an FP16N neighbour is projected from its codes
 // and scaled by its norm after the colour product.  WIDEN: an FP32 input half-vector
@@ -134,6 +132,7 @@ __device__ __forceinline__ void stage_lds_body(const StageArgs &A, int sb, int t
     static_assert(RED != 4 || (CLOVER && POST == 0 && sizeof(R) == 8), "reduction 4: FP64 clover stages");
     static_assert(RED != 5 || (!CLOVER && POST == 2 && sizeof(R) == 8), "reduction 5: FP64 residual stages");
     static_assert(RED < 6 || (sizeof(R) == 8 && (RED == 6 ? POST == 0 : POST == 2)), "modes 6, 7: FP64 stages");
+    const bool w_zero = RED == 1 && w_is_zero(A, sb * kLdsSites, kLdsSites);   // uniform
 #pragma unroll 1
     for (int rw = 0; rw < RW; ++rw) {
         const int slot = A.tile_slots[tile * NT + rw * 4 + wave];
@@ -265,13 +264,15 @@ __device__ __forceinline__ void stage_lds_body(const StageArgs &A, int sb, int t
                 SpinorIO<P>::store(A.w.at(slot), g.vh, hw, xw);
             }
             if (RED == 1) {
-                cplx<R> ww[12];
-                SpinorIO<P>::load(A.w.at(slot), g.vh, h, ww);
-                cplx<R> d = {R(0), R(0)};
+                if (!w_zero) {
+                    cplx<R> ww[12];
+                    SpinorIO<P>::load(A.w.at(slot), g.vh, h, ww);
+                    cplx<R> d = {R(0), R(0)};
 #pragma unroll
-                for (int c = 0; c < 12; ++c) cmac_conj(d, ww[c], res[c]);
-                part[0] = d.re;
-                part[1] = d.im;
+                    for (int c = 0; c < 12; ++c) cmac_conj(d, ww[c], res[c]);
+                    part[0] = d.re;
+                    part[1] = d.im;
+                }
             } else if (RED == 2) {
                 cplx<R> d = {R(0), R(0)};
                 R n2 = R(0);
@@ -308,10 +309,12 @@ template <class P, int RW, bool DAG, bool CLOVER, bool PRE, int POST, int RED>
 __global__ __launch_bounds__(256) void stage_lds_kernel(StageArgs A) {
     const int nt = *A.ntiles;
     int first, end, step;
-    stage_item_range(nt * A.nsb, A.dispatch_order, first, end, step);
+    stage_item_range(nt * A.nsb_win, A.dispatch_order, first, end, step);
     for (int w = first; w < end; w += step) {
         int sb, tile;
-        stage_item(w, A.site_major, A.nsb, nt, sb, tile);
+        stage_item(w, A.site_major, A.nsb_win, nt, sb, tile);
+        sb += A.sb_first;
+        if (sb >= A.nsb) sb -= A.nsb;
         sb = tiled_block(sb, A.nyb, A.tz, A.tt, A.g.lz);
         if (block_outside(A.win, sb * kLdsSites, min(kLdsSites, A.g.vh - sb * kLdsSites), A.g.vh)) continue;
         stage_lds_body<P, RW, DAG, CLOVER, PRE, POST, RED>(A, sb, tile);
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(256) void stage_lds_kernel(StageArgs A) {
 // ---------------------------------------------------------------------------
 template <class P, int RW, bool DAG, bool CLOVER, bool PRE, int POST, int RED>
 inline void launch_lds_t(const StageArgs &a, hipStream_t st) {
-    const int nblk = stage_grid(a.nsb * a.ntiles_max, a.grid_cap);
+    const int nblk = stage_grid(a.nsb_win * a.ntiles_max, a.grid_cap);
     hipLaunchKernelGGL((stage_lds_kernel<P, RW, DAG, CLOVER, PRE, POST, RED>), dim3(nblk), dim3(256), 0, st, a);
 }
 

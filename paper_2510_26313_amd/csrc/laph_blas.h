@@ -21,7 +21,12 @@ struct BlasArgs {
     Operand x64, r64;            // FP64 solution and residual
     const int *flist = nullptr;  // flagged mode: slots taking a reliable update
     const int *nflist = nullptr; // device scalar: entries of flist
-    SiteWindow win;              // norm2 / copy64: the sources are zero outside it (not read)
+    SiteWindow win;              // norm2 / copy64: the sources are zero outside it (not read);
+                                 // p / s / xr updates: the sites updated
+    SiteWindow win_rh;           // r^ is zero outside it (not read by the xr update) ...
+    int *rh_full = nullptr;      // ... unless this device flag is set (a restart replaced r^)
+    SiteWindow win_pv;           // p update: p and v are zero outside it (not read)
+    int sb_first = 0;            // p / s updates: first site block of the window (set by the launcher)
 };
 
 // Input / output of the flagged-slot compaction (blas_flag_tiles).
@@ -44,6 +49,8 @@ struct FinArgs {
     SlotState *st = nullptr;
     const double *partials = nullptr;
     int max_restarts = 10;
+    int first = 0;      // a windowed producer wrote the partials of `count` blocks from `first` (cyclic)
+    int count = 0;
 };
 
 laph_status blas_p_update(const Ctx &c, const BlasArgs &a, int prec);

@@ -32,6 +32,9 @@ struct SlotState {
     int xlo_zero;     // 1: x_lo is zero (its memory is stale and not read) until the next x/r update
 };
 
+constexpr int kBlock = 256;     // sites per workgroup of the register form and of the vector kernels
+constexpr int kLdsSites = 64;   // sites per workgroup of the LDS form
+
 // Two forms of the stencil stage kernel: RHS tiles held in registers by one
 // thread, or RHS-parallel waves sharing links staged in LDS.
 enum { kFormRegister = 0, kFormLds = 1 };
@@ -161,7 +164,10 @@ struct StageSpec {
     const SlotState *slots = nullptr;   // may be null when flagged == 0
     double *partials = nullptr;         // [slot][3][pstride]
     int pstride = 0;                    // partials per quantity per slot (>= stage_nsb)
-    SiteWindow win;                     // output sites computed (the others untouched); red == 0 only
+    SiteWindow win;                     // output sites computed (the others untouched; a reduction leaves
+                                        // the partials of blocks outside it unwritten)
+    SiteWindow win_w;                   // red == 1: w is zero outside this window (not read there) ...
+    const int *w_full = nullptr;        // ... unless this device flag is set
 };
 // site blocks of a stage launch (= partial sums it writes per quantity and slot)
 int stage_nsb(const Ctx &c, int form);

@@ -154,6 +154,19 @@ __host__ __device__ inline bool block_outside(const SiteWindow &w, int h0, int c
     return d >= w.n && d + cnt <= vh;
 }
 
+// the blocks of `size` consecutive sites (nb in all) that overlap the window: a cyclic range
+// of block indices from *first; every block when it covers the lattice
+inline int window_blocks(const SiteWindow &w, int size, int nb, int vh, int *first) {
+    *first = 0;
+    if (w.n <= 0 || w.n >= vh) return nb;
+    const int f = w.lo / size;
+    const int end = w.lo + w.n;
+    const int cnt = end <= vh ? (end - 1) / size - f + 1 : nb - f + (end - vh - 1) / size + 1;
+    if (cnt >= nb) return nb;
+    *first = f;
+    return cnt;
+}
+
 // the timeslices t0 - k .. t0 + k (periodic in t); every site when they cover the lattice
 inline SiteWindow slab_window(const Geom &g, int t0, int k) {
     SiteWindow w;
@@ -309,11 +322,14 @@ struct SpinorIO<F16N> {
 // gauge link load (one link)
 // ---------------------------------------------------------------------------
 struct GaugePtrs {
-    // [parity][mu] base pointers of the per-(parity, mu) arrays
-    const char *f64[2][4];
-    const char *f32[2][4];
-    const char *f16a[2][4];
-    const char *f16b[2][4];
+    // base and size of the per-(parity, mu) arrays of each format, (parity, mu) = (0,0), (0,1), ...
+    // (addresses by arithmetic: tables of 32 pointers were a third of the stencil's arguments)
+    const char *b64, *b32, *b16a, *b16b;
+    size_t s64, s32, s16a, s16b;
+    __host__ __device__ const char *f64(int p, int mu) const { return b64 + (p * 4 + mu) * s64; }
+    __host__ __device__ const char *f32(int p, int mu) const { return b32 + (p * 4 + mu) * s32; }
+    __host__ __device__ const char *f16a(int p, int mu) const { return b16a + (p * 4 + mu) * s16a; }
+    __host__ __device__ const char *f16b(int p, int mu) const { return b16b + (p * 4 + mu) * s16b; }
 };
 
 template <class R>
@@ -331,7 +347,7 @@ template <>
 struct GaugeIO<F64> {
     static __device__ __forceinline__ void load(const GaugePtrs &g, int parity, int mu, int vh, int h,
                                                 cplx<double> (&u)[9]) {
-        const double2 *p = reinterpret_cast<const double2 *>(g.f64[parity][mu]);
+        const double2 *p = reinterpret_cast<const double2 *>(g.f64(parity, mu));
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
             double2 v = p[(size_t)k * vh + h];
@@ -344,7 +360,7 @@ template <>
 struct GaugeIO<F32> {
     static __device__ __forceinline__ void load(const GaugePtrs &g, int parity, int mu, int vh, int h,
                                                 cplx<float> (&u)[9]) {
-        const float4 *p = reinterpret_cast<const float4 *>(g.f32[parity][mu]);
+        const float4 *p = reinterpret_cast<const float4 *>(g.f32(parity, mu));
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             float4 v = p[(size_t)j * vh + h];
@@ -359,8 +375,8 @@ template <>
 struct GaugeIO<F16N> {
     static __device__ __forceinline__ void load(const GaugePtrs &g, int parity, int mu, int vh, int h,
                                                 cplx<float> (&u)[9]) {
-        half8 a = reinterpret_cast<const half8 *>(g.f16a[parity][mu])[h];
-        half4 b = reinterpret_cast<const half4 *>(g.f16b[parity][mu])[h];
+        half8 a = reinterpret_cast<const half8 *>(g.f16a(parity, mu))[h];
+        half4 b = reinterpret_cast<const half4 *>(g.f16b(parity, mu))[h];
 #pragma unroll
         for (int k = 0; k < 4; ++k) u[k] = {(float)a[2 * k], (float)a[2 * k + 1]};
         u[4] = {(float)b[0], (float)b[1]};

@@ -77,6 +77,7 @@ class Solver {
         int *tile64f_slots = nullptr, *tile64f_mass = nullptr;  // FP64 tiles of the flagged slots
         int *list = nullptr, *slot_mass = nullptr, *flist = nullptr;
         int *ntiles = nullptr, *nlist = nullptr, *ntiles64 = nullptr, *ntiles64f = nullptr, *nflist = nullptr;
+        int *rh_full = nullptr;       // set on the device when a restart gives r^ the whole lattice
         int *ints = nullptr;          // integer region the tables are carved from
         size_t nints = 0, nints_used = 0;
     };
@@ -107,12 +108,14 @@ class Solver {
     std::vector<int> mass;
     std::vector<int> host_ints;
     std::vector<SlotState> host_st;
+    SiteWindow rh_win;   // r^ is zero outside it unless ws.rh_full is set (every site: no window)
+    int src_t0 = 0;
     hipGraphExec_t graph_exec = nullptr;
     int graph_k = 0;
 
     void carve_tables();
     BlasArgs blas(int list_max) const;
-    FinArgs fin(int list_max, int nsb = 0) const;
+    FinArgs fin(int list_max, int nsb = 0, SiteWindow win = SiteWindow(), int bs = 0) const;
     Tiles tiles(bool f64, bool flagged = false) const;
     laph_status upload_tables(const std::vector<int> &slots);
     laph_status download_state();
@@ -122,7 +125,8 @@ class Solver {
                       SiteWindow win = SiteWindow());
     laph_status clover(int parity, int inverse, Operand in, Operand out, int post, Operand y, double a, double b,
                        int nlist, SiteWindow win = SiteWindow());
-    laph_status iteration();
+    void drop_graph();
+    laph_status iteration(int grow);
     laph_status run_iterations(int k);
     laph_status load_sources(const SourceSpec &src);
     laph_status load_even_source(const SourceSpec &src, SiteWindow win);

@@ -40,9 +40,9 @@ __global__ __launch_bounds__(kSetupBlock) void gauge_pack_kernel(Geom g, const d
         cplx<double> det = u[0] * (u[4] * u[8] - u[5] * u[7]) - u[1] * (u[3] * u[8] - u[5] * u[6]) +
                            u[2] * (u[3] * u[7] - u[4] * u[6]);
         dev = fmax(dev, fmax(fabs(det.re - 1.0), fabs(det.im)));
-        double2 *d64 = reinterpret_cast<double2 *>(const_cast<char *>(gp.f64[p][mu]));
+        double2 *d64 = reinterpret_cast<double2 *>(const_cast<char *>(gp.f64(p, mu)));
         for (int k = 0; k < 9; ++k) d64[(size_t)k * g.vh + h] = make_double2(u[k].re, u[k].im);
-        float4 *d32 = reinterpret_cast<float4 *>(const_cast<char *>(gp.f32[p][mu]));
+        float4 *d32 = reinterpret_cast<float4 *>(const_cast<char *>(gp.f32(p, mu)));
         for (int j = 0; j < 3; ++j)
             d32[(size_t)j * g.vh + h] = make_float4((float)u[2 * j].re, (float)u[2 * j].im,
                                                     (float)u[2 * j + 1].re, (float)u[2 * j + 1].im);
@@ -56,8 +56,8 @@ __global__ __launch_bounds__(kSetupBlock) void gauge_pack_kernel(Geom g, const d
         b4[1] = (_Float16)u[4].im;
         b4[2] = (_Float16)u[5].re;
         b4[3] = (_Float16)u[5].im;
-        reinterpret_cast<half8 *>(const_cast<char *>(gp.f16a[p][mu]))[h] = a8;
-        reinterpret_cast<half4 *>(const_cast<char *>(gp.f16b[p][mu]))[h] = b4;
+        reinterpret_cast<half8 *>(const_cast<char *>(gp.f16a(p, mu)))[h] = a8;
+        reinterpret_cast<half4 *>(const_cast<char *>(gp.f16b(p, mu)))[h] = b4;
     }
     if (!(dev <= 1e300)) dev = 1e300;  // NaN -> huge
     atomicMax(maxdev, (unsigned long long)__double_as_longlong(dev));
@@ -121,8 +121,7 @@ __device__ __forceinline__ LinkRef link64(const Geom &g, const GaugePtrs &gp, co
     if (c[NU] < 0) c[NU] += ext[NU];
     if (c[NU] == ext[NU]) c[NU] = 0;
     const int par = (c[0] + c[1] + c[2] + c[3]) & 1;
-    const char *base = par ? gp.f64[1][dir] : gp.f64[0][dir];
-    return {reinterpret_cast<const double2 *>(base) + cb_index(g, c[0], c[1], c[2], c[3]), (size_t)g.vh};
+    return {reinterpret_cast<const double2 *>(gp.f64(par, dir)) + cb_index(g, c[0], c[1], c[2], c[3]), (size_t)g.vh};
 }
 
 // s += a b (fused multiply-add chain), SUB: s -= a b

@@ -115,6 +115,7 @@ void Solver::carve_tables() {
     ws.flist = ws.tile64f_mass + ns;
     ws.ntiles64f = ws.flist + ns;
     ws.nflist = ws.ntiles64f + 1;
+    ws.rh_full = ws.nflist + 1;
     ws.nints_used = (size_t)(ws.ntiles + 3 - ints);
 }
 
@@ -194,8 +195,11 @@ laph_status Solver::init(Ctx &ctx, int nslots, const laph_solve_params &params, 
     return LAPH_OK;
 }
 
-Solver::~Solver() {
+Solver::~Solver() { drop_graph(); }
+
+void Solver::drop_graph() {
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
+    graph_exec = nullptr;
 }
 
 BlasArgs Solver::blas(int list_max) const {
@@ -218,15 +222,18 @@ BlasArgs Solver::blas(int list_max) const {
     a.r64 = ws.E2;
     a.flist = ws.flist;
     a.nflist = ws.nflist;
+    a.win_rh = rh_win;
+    a.rh_full = ws.rh_full;
     return a;
 }
 
-FinArgs Solver::fin(int list_max, int nsb) const {
+FinArgs Solver::fin(int list_max, int nsb, SiteWindow win, int bs) const {
     FinArgs f;
     f.list = ws.list;
     f.nlist = ws.nlist;
     f.nlist_max = list_max;
     f.nsb = nsb > 0 ? nsb : nsb256;
+    f.count = window_blocks(win, bs, f.nsb, c->g.vh, &f.first);
     f.pstride = pstride;
     f.st = ws.st;
     f.partials = ws.partials;
@@ -335,6 +342,8 @@ laph_status Solver::stage(int sprec, int out_parity, Operand in, Operand out, in
     s.partials = ws.partials;
     s.pstride = pstride;
     s.win = win;
+    s.win_w = rh_win;   // reduction 1: w is r^
+    s.w_full = ws.rh_full;
     return launch_stage(*c, s);
 }
 
@@ -358,24 +367,38 @@ laph_status Solver::clover(int parity, int inverse, Operand in, Operand out, int
 }
 
 // ---- one BiCGStab iteration (all kernels device-driven) ---------------------
-laph_status Solver::iteration() {
+// grow = j > 0: iteration j of a solve whose b_hat lives on the timeslices t0 +- 1.  Every
+// stage widens the support of its input by one timeslice, so r and p enter iteration j on
+// t0 +- (4 j - 3), v and s live on +- (4 j - 1), t and the new r on +- (4 j + 1): the kernels
+// skip the sites beyond, where every vector is exactly zero (p and tmp are zeroed at the
+// start, the others are not read there).  The skipped sums are sums of zeros, so the
+// iterates do not change by a bit.
+laph_status Solver::iteration(int grow) {
     const Operand none;
     BlasArgs a = blas(ns);
-    FinArgs f = fin(ns);
+    auto reach = [&](int k) { return grow > 0 ? slab_window(c->g, src_t0, k) : SiteWindow(); };
+    const SiteWindow wp = reach(4 * grow - 3), wv = reach(4 * grow - 1), wt = reach(4 * grow + 1);
+    const int bs = form == kFormLds ? kLdsSites : kBlock;
+    a.win = wp;
+    a.win_pv = grow > 1 ? reach(4 * grow - 5) : SiteWindow();   // (the first p is r)
     LAPH_TRY(blas_p_update(*c, a, prec));
     // v = M_hat p,  <r^, v>
-    LAPH_TRY(stage(prec, 1, ws.p, ws.tmp, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 0, none, 0));
-    LAPH_TRY(stage(prec, 0, ws.tmp, ws.v, 1, 0, none, 0, 1, ws.p, 1.0, none, 0, -0.25, 1, ws.rh, 0));
-    LAPH_TRY(blas_finalize(*c, fin(ns, nsb_inner), kFinAlpha));
+    LAPH_TRY(stage(prec, 1, ws.p, ws.tmp, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 0, none, 0, reach(4 * grow - 2)));
+    LAPH_TRY(stage(prec, 0, ws.tmp, ws.v, 1, 0, none, 0, 1, ws.p, 1.0, none, 0, -0.25, 1, ws.rh, 0, wv));
+    LAPH_TRY(blas_finalize(*c, fin(ns, nsb_inner, wv, bs), kFinAlpha));
     // s = r - alpha v (in r)
+    a.win = wv;
     LAPH_TRY(blas_s_update(*c, a, prec));
     // t = M_hat s,  <t, s>, |t|^2
-    LAPH_TRY(stage(prec, 1, ws.r, ws.tmp, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 0, none, 0));
-    LAPH_TRY(stage(prec, 0, ws.tmp, ws.t, 1, 0, none, 0, 1, ws.r, 1.0, none, 0, -0.25, 2, none, 0));
-    LAPH_TRY(blas_finalize(*c, fin(ns, nsb_inner), kFinOmega));
+    LAPH_TRY(stage(prec, 1, ws.r, ws.tmp, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 0, none, 0, reach(4 * grow)));
+    LAPH_TRY(stage(prec, 0, ws.tmp, ws.t, 1, 0, none, 0, 1, ws.r, 1.0, none, 0, -0.25, 2, none, 0, wt));
+    LAPH_TRY(blas_finalize(*c, fin(ns, nsb_inner, wt, bs), kFinOmega));
     // x_lo += alpha p + omega s;  r = s - omega t;  rho, |r|^2, update decision
+    a.win = wt;
     LAPH_TRY(blas_xr_update(*c, a, prec));
-    LAPH_TRY(blas_finalize(*c, f, kFinRho));
+    LAPH_TRY(blas_finalize(*c, fin(ns, 0, wt, kBlock), kFinRho));
+    a.win = SiteWindow();
+    FinArgs f = fin(ns);
     // compact the slots flagged for a reliable update (list and FP64 tiles)
     FlagArgs fl;
     fl.tile_slots = ws.tile64_slots;
@@ -412,18 +435,15 @@ laph_status Solver::iteration() {
 
 laph_status Solver::run_iterations(int k) {
     if (!p.use_graph) {
-        for (int i = 0; i < k; ++i) LAPH_TRY(iteration());
+        for (int i = 0; i < k; ++i) LAPH_TRY(iteration(0));
         return LAPH_OK;
     }
     if (!graph_exec || graph_k != k) {
-        if (graph_exec) {
-            (void)hipGraphExecDestroy(graph_exec);
-            graph_exec = nullptr;
-        }
+        drop_graph();
         hipGraph_t graph = nullptr;
         LAPH_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
         laph_status st = LAPH_OK;
-        for (int i = 0; i < k && st == LAPH_OK; ++i) st = iteration();
+        for (int i = 0; i < k && st == LAPH_OK; ++i) st = iteration(0);
         hipError_t e = hipStreamEndCapture(c->stream, &graph);
         if (st != LAPH_OK) {
             if (graph) (void)hipGraphDestroy(graph);
@@ -495,6 +515,10 @@ laph_status Solver::solve(const SourceSpec &src, const std::vector<int> &slot_ma
     const SiteWindow w_src = slab ? slab_window(c->g, src.t0, 0) : SiteWindow();
     const SiteWindow w_hat = slab ? slab_window(c->g, src.t0, 1) : SiteWindow();
     const SiteWindow w_clv = slab ? slab_window(c->g, src.t0, 2) : SiteWindow();
+    // r^ = r0 stays on the slab until a restart replaces it
+    if (w_hat.lo != rh_win.lo || w_hat.n != rh_win.n) drop_graph();
+    rh_win = w_hat;
+    src_t0 = src.t0;
     // |B|^2 and the stopping threshold on the even-odd residual
     LAPH_TRY(load_sources(src));
     BlasArgs a_src = a;
@@ -535,7 +559,8 @@ laph_status Solver::solve(const SourceSpec &src, const std::vector<int> &slot_ma
         }
         // partials of the FP64 stage (warm start) or of the norm kernel
         LAPH_TRY(blas_finalize(*c, have_x ? fin(ncur, nsb64) : f, kFinR64));
-        LAPH_TRY(blas_lower(*c, a, prec, kModeActive, 1));
+        // r^ = r: the slab of b_hat on the first pass, the whole lattice on the others
+        LAPH_TRY(blas_lower(*c, a, prec, kModeActive, pass == 0 ? 1 : 2));
         LAPH_TRY(blas_finalize(*c, f, kFinInit));
         // iterate; the captured graph always spans ns slots (tables say which are live)
         LAPH_TRY(download_state());
@@ -544,9 +569,27 @@ laph_status Solver::solve(const SourceSpec &src, const std::vector<int> &slot_ma
             if (host_st[s].status == LAPH_RHS_ACTIVE) active.push_back(s);
         LAPH_TRY(upload_tables(active));
         const int K = p.graph_iters > 0 ? p.graph_iters : 8;
+        // iterations whose vectors do not reach the whole lattice yet run as plain launches on
+        // their windows, where that pays: below about 2^20 site-RHS an iteration takes less
+        // than 0.5 ms, about 20 launches of 5 us, and the graph's replay is as fast
+        int grow = 0;
+        if (slab && pass == 0 && (size_t)c->g.vh * ncur >= ((size_t)1 << 20))
+            while (2 * (4 * (grow + 1) - 5) + 1 < c->g.lt) ++grow;
+        if (grow == 1) grow = 0;   // (a lattice of few timeslices)
+        if (grow > 0) {
+            LAPH_HIP(hipMemsetAsync(ws.p.base, 0, ws.p.stride * n, c->stream));
+            LAPH_HIP(hipMemsetAsync(ws.tmp.base, 0, ws.tmp.stride * n, c->stream));
+        }
         int guard = 0;
         while (!active.empty()) {
-            LAPH_TRY(run_iterations(K));
+            if (guard * K < grow) {
+                for (int i = 0; i < K; ++i) {
+                    const int j = guard * K + i + 1;
+                    LAPH_TRY(iteration(j <= grow ? j : 0));
+                }
+            } else {
+                LAPH_TRY(run_iterations(K));
+            }
             LAPH_TRY(download_state());
             std::vector<int> still;
             for (int s : active)
