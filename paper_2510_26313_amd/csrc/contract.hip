@@ -15,12 +15,18 @@
 // direct global-to-LDS loads, two chunks deep, so the next chunk arrives while the
 // matrix cores work on the current one; each wave forms its A and B fragments from
 // LDS (the cross products are never stored).  B_p is antisymmetric in every index pair, so
-// only l < m < n is accumulated (a wave runs only the row blocks with some l below
-// its pairs' largest m), and the reduction writes all six orderings with their signs and
-// zeros where an index repeats.  K is split over workgroups for occupancy; the
-// reduction sums the slices in a fixed order.
+// each set of three indices is accumulated once (see PairTable), and the reduction writes
+// all six orderings with their signs and zeros where an index repeats.  K is split over
+// workgroups for occupancy; the reduction sums the slices in a fixed order.
+//
+// Doublets of several momenta share their products: with p.x = (px x + py y) + pz z the
+// momenta of one (px, py) -- up to an overall sign, which conjugates and transposes --
+// need one product per z plane, S(z)[l][m] = sum_xy e^{-i (px x + py y)} conj(V_l) V_m,
+// and differ only in the phases their planes are summed with.  For (px, py) = -(px, py)
+// S(z) is Hermitian and only the 16x16 blocks on and above its diagonal are formed.
 #include <algorithm>
 #include <cmath>
+#include <vector>
 
 #include "laph_solver.h"
 
@@ -42,24 +48,66 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 struct ContractArgs {
     int lx, ly, lz, lt, vs;
     int nev;
-    int ncol;             // doublets: nev; triplets: nev (nev - 1) / 2 pairs (m < n, m-major)
+    int ncol;             // doublets: nev; triplets: columns of the PairTable
     int ntile;            // column tiles per (t, p)
     int nsplit;           // K slices
     int nchunk;           // K chunks of kCS sites
     int nmom;
     int mom[3 * kCMaxMom];
+    int out[kCMaxMom];    // index of each momentum in the result
+    int plane;            // > 0: K slice = z plane of this many sites (doublets by planes), 0: even slices
+    int herm;             // doublets: only the 16x16 blocks on and above the diagonal
     const double2 *V;     // [lt][nev][vs][3]
     double2 *scratch;     // [nsplit][nmom][lt][nev][ncol]
 };
 
-// first column of pair row m in the m-major list of pairs m < n
-__host__ __device__ __forceinline__ int pair_base(int m, int nev) { return m * nev - m * (m + 1) / 2; }
-
-__device__ __forceinline__ void pair_of(int q, int nev, int &m, int &n) {
-    m = 0;
-    while (m + 1 < nev && pair_base(m + 1, nev) <= q) ++m;
-    n = q - pair_base(m, nev) + m + 1;
-}
+// Columns of the triplets.  With the indices in blocks of 16, a sorted triple a < b < c in
+// blocks A <= B <= C is the product of
+//   row c with the pair (a, b)  if A == B        (cyclic orders: all with sign +)
+//   row a with the pair (b, c)  otherwise,
+// so the pairs inside a block need every row block, the pairs of two blocks i < j the row
+// blocks below i, and pairs with i = 0 are not needed at all.  Columns are listed by falling
+// row count (pairs inside blocks 0, 1, ...; then pairs (i, j > i), i = nblk - 2 .. 1), so a wave runs a
+// prefix of the row blocks.  Against all pairs m < n with the rows below m, as the list
+// was before: nev 64 47 104 products of 16 issued for 41 664 triples instead of 58 300, and
+// 1248 cross products instead of 2016.
+struct PairTable {
+    int nev, nblk;
+    __host__ __device__ explicit PairTable(int n) : nev(n), nblk((n + 15) / 16) {}
+    __host__ __device__ int width(int i) const { return i + 1 < nblk ? 16 : nev - 16 * i; }
+    __host__ __device__ int inside(int i) const { return 120 * i; }   // first column of block i's pairs
+    __host__ __device__ int n_inside() const { return inside(nblk - 1) + width(nblk - 1) * (width(nblk - 1) - 1) / 2; }
+    // first column of the pairs (block i, later blocks)
+    __host__ __device__ int across(int i) const {
+        int c = n_inside();
+        for (int k = nblk - 2; k > i; --k) c += 16 * (nev - 16 * (k + 1));
+        return c;
+    }
+    __host__ __device__ int ncol() const { return across(0); }
+    __host__ __device__ int col(int m, int n) const {   // m < n
+        const int i = m >> 4, u = m & 15, w = width(i);
+        if (i == n >> 4) return inside(i) + u * w - u * (u + 1) / 2 + (n & 15) - u - 1;
+        return across(i) + u * (nev - 16 * (i + 1)) + n - 16 * (i + 1);
+    }
+    // the pair of a column and the row blocks it needs
+    __host__ __device__ void pair(int q, int &m, int &n, int &rows) const {
+        if (q < n_inside()) {
+            const int i = q / 120 < nblk - 1 ? q / 120 : nblk - 1, w = width(i);
+            int e = q - inside(i), u = 0;
+            while (e >= w - 1 - u) e -= w - 1 - u++;
+            m = 16 * i + u;
+            n = m + 1 + e;
+            rows = nblk;
+            return;
+        }
+        int i = nblk - 2, e = q - n_inside();
+        while (e >= 16 * (nev - 16 * (i + 1))) e -= 16 * (nev - 16 * (i-- + 1));
+        const int w = nev - 16 * (i + 1);
+        m = 16 * i + e / w;
+        n = 16 * (i + 1) + e % w;
+        rows = i;
+    }
+};
 
 // One staged chunk: the wave's A fragments (R row blocks) and B fragments (NCB column
 // blocks) per group of 4 K, then the R x NCB x 4 real products as straight-line code,
@@ -181,28 +229,31 @@ __global__ __launch_bounds__(kCB) void contract_kernel(ContractArgs A) {
     const int nev = A.nev;
 
     // this lane's column per block, the pair behind it, and the number of 16-row
-    // blocks the wave needs (wave-uniform: triplets need l < m, m at most the m of the
-    // wave's last pair)
+    // blocks the wave needs (wave-uniform)
     int col[NCB], cm[NCB], cn[NCB];
-    int rows_hi = 0;
+    int nact = 0;
+    // with half of a Hermitian block row to do, the waves take the columns in turn, so that
+    // the workgroups sharing a CU load its SIMDs evenly
+    const int wcol = MODE == 0 && A.herm ? (wave + bid) & 3 : wave;
 #pragma unroll
     for (int j = 0; j < NCB; ++j) {
-        const int c0 = tile * kCols + (wave * NCB + j) * 16;
+        const int c0 = tile * kCols + (wcol * NCB + j) * 16;
         col[j] = c0 + (lane & 15);
         cm[j] = 0;
         cn[j] = 0;
         if (c0 >= A.ncol) continue;   // a block past the last column: zero B (V_0 x V_0, or column 0 unread)
         if (MODE == 1) {
-            if (col[j] < A.ncol) pair_of(col[j], nev, cm[j], cn[j]);
-            int mlast, nlast;
-            pair_of(min(c0 + 15, A.ncol - 1), nev, mlast, nlast);
-            rows_hi = max(rows_hi, mlast);
+            const PairTable pt(nev);
+            int rows;
+            if (col[j] < A.ncol) pt.pair(col[j], cm[j], cn[j], rows);
+            int m0, n0;
+            pt.pair(c0, m0, n0, rows);   // the block's first column needs the most rows
+            nact = max(nact, rows);
         } else {
             cm[j] = col[j] < A.ncol ? col[j] : 0;
-            rows_hi = nev;
+            nact = A.herm ? wcol + 1 : (nev + 15) / 16;
         }
     }
-    const int nact = min(4, (rows_hi + 15) / 16);
 
     d4 cre[4][NCB], cim[4][NCB];
 #pragma unroll
@@ -213,16 +264,18 @@ __global__ __launch_bounds__(kCB) void contract_kernel(ContractArgs A) {
             cim[i][j] = d4{0, 0, 0, 0};
         }
     const int mx = A.mom[3 * p], my = A.mom[3 * p + 1], mz = A.mom[3 * p + 2];
-    const int ch0 = (int)((long)A.nchunk * split / A.nsplit), ch1 = (int)((long)A.nchunk * (split + 1) / A.nsplit);
+    const int ch0 = A.plane ? 0 : (int)((long)A.nchunk * split / A.nsplit);
+    const int ch1 = A.plane ? A.nchunk : (int)((long)A.nchunk * (split + 1) / A.nsplit);
+    const int first = A.plane * split, end = A.plane ? first + A.plane : A.vs;   // sites of this slice
     const double2 *Vt = A.V + (size_t)t * nev * A.vs * 3;
     const int n3 = 3 * A.vs;
     // e^{-2 pi i (nx x / Lx + ny y / Ly + nz z / Lz)} of the chunk's sites, integer parts
-    // reduced first; zero for sites past the timeslice
+    // reduced first; zero for sites past the slice
     auto phases = [&](double2 *ph, int s0) {
         if (tid < kCS) {
             const int s = s0 + tid;
             double2 v = make_double2(0.0, 0.0);
-            if (s < A.vs) {
+            if (s < end) {
                 const int x = s % A.lx, y = (s / A.lx) % A.ly, z = s / (A.lx * A.ly);
                 const int qx = ((mx * x) % A.lx + A.lx) % A.lx;
                 const int qy = ((my * y) % A.ly + A.ly) % A.ly;
@@ -234,23 +287,23 @@ __global__ __launch_bounds__(kCB) void contract_kernel(ContractArgs A) {
         }
     };
     if (ch0 < ch1) {
-        stage_chunk(bufA, Vt, nev, n3, ch0 * kCS, wave, lane);
-        phases(phA, ch0 * kCS);
+        stage_chunk(bufA, Vt, nev, n3, first + ch0 * kCS, wave, lane);
+        phases(phA, first + ch0 * kCS);
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     for (int ch = ch0; ch < ch1; ch += 2) {
         if (ch + 1 < ch1) {
-            stage_chunk(bufB, Vt, nev, n3, (ch + 1) * kCS, wave, lane);
-            phases(phB, (ch + 1) * kCS);
+            stage_chunk(bufB, Vt, nev, n3, first + (ch + 1) * kCS, wave, lane);
+            phases(phB, first + (ch + 1) * kCS);
         }
         chunk_dispatch<MODE, NCB>(nact, bufA, phA, lane, cm, cn, cre, cim);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (ch + 1 >= ch1) break;
         if (ch + 2 < ch1) {
-            stage_chunk(bufA, Vt, nev, n3, (ch + 2) * kCS, wave, lane);
-            phases(phA, (ch + 2) * kCS);
+            stage_chunk(bufA, Vt, nev, n3, first + (ch + 2) * kCS, wave, lane);
+            phases(phA, first + (ch + 2) * kCS);
         }
         chunk_dispatch<MODE, NCB>(nact, bufB, phB, lane, cm, cn, cre, cim);
         __builtin_amdgcn_s_waitcnt(0);
@@ -273,7 +326,7 @@ __global__ __launch_bounds__(kCB) void contract_kernel(ContractArgs A) {
 }
 
 // Phi[p][t][l][m] = sum over K slices
-__global__ void doublet_reduce_kernel(ContractArgs A, double2 *phi, int p_begin, int nmom_total) {
+__global__ void doublet_reduce_kernel(ContractArgs A, double2 *phi) {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     const long per = (long)A.lt * A.nev * A.nev;
     if (idx >= per * A.nmom) return;
@@ -285,13 +338,12 @@ __global__ void doublet_reduce_kernel(ContractArgs A, double2 *phi, int p_begin,
         s.x += v.x;
         s.y += v.y;
     }
-    (void)nmom_total;
-    phi[(size_t)(p_begin + p) * per + r] = s;
+    phi[(size_t)A.out[p] * per + r] = s;
 }
 
 // B[p][t][l][m][n]: the sum over K slices of the sorted triple's entry, with the
 // sign of the permutation that sorts (l, m, n); zero when two indices coincide
-__global__ void triplet_reduce_kernel(ContractArgs A, double2 *B, int p_begin) {
+__global__ void triplet_reduce_kernel(ContractArgs A, double2 *B) {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     const int nev = A.nev;
     const long per = (long)A.lt * nev * nev * nev;
@@ -309,16 +361,77 @@ __global__ void triplet_reduce_kernel(ContractArgs A, double2 *B, int p_begin) {
         if (a > b) { int q = a; a = b; b = q; sg = -sg; }
         if (b > c) { int q = b; b = c; c = q; sg = -sg; }
         if (a > b) { int q = a; a = b; b = q; sg = -sg; }
-        const int q = pair_base(b, nev) + (c - b - 1);
+        const PairTable pt(nev);
+        const bool low = a >> 4 == b >> 4;   // (a, b) in one block: row c, else row a
+        const int q = low ? pt.col(a, b) : pt.col(b, c), row = low ? c : a;
         for (int sp = 0; sp < A.nsplit; ++sp) {
-            const double2 v = A.scratch[((((size_t)sp * A.nmom + p) * A.lt + t) * nev + a) * A.ncol + q];
+            const double2 v = A.scratch[((((size_t)sp * A.nmom + p) * A.lt + t) * nev + row) * A.ncol + q];
             s.x += v.x;
             s.y += v.y;
         }
         s.x *= sg;
         s.y *= sg;
     }
-    B[(size_t)(p_begin + p) * per + r] = s;
+    B[(size_t)A.out[p] * per + r] = s;
+}
+
+// Doublets by planes: Phi of up to kPlaneMom momenta of one (px, py) from S(z).  A member with
+// flip has the opposite (px, py): Phi_p[m][l] = conj(sum_z e^{+i pz z} S(z)[l][m]).  herm: S(z)
+// holds the blocks on and above the diagonal and its other half follows the same way.
+constexpr int kPlaneMom = 8;
+constexpr int kPlaneZ = 128;   // phases kept in LDS
+
+struct PlaneArgs {
+    int lt, lz, nev, n, herm;
+    int mz[kPlaneMom], flip[kPlaneMom], out[kPlaneMom];
+    const double2 *S;     // [lz][lt][nev][nev]
+    double2 *phi;         // [momenta][lt][nev][nev]
+};
+
+template <int NM>
+__global__ __launch_bounds__(256) void doublet_planes_kernel(PlaneArgs A) {
+    __shared__ double2 ph[NM][kPlaneZ];
+    const int nev = A.nev;
+    const long per = (long)A.lt * nev * nev;
+    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+    const int m = (int)(idx % nev), l = (int)((idx / nev) % nev);
+    const bool live = idx < per && !(A.herm && (l >> 4) > (m >> 4));
+    double2 s[NM], d[NM];   // sums with e^{-i pz z} and e^{+i pz z}
+#pragma unroll
+    for (int k = 0; k < NM; ++k) s[k] = d[k] = make_double2(0.0, 0.0);
+    for (int z0 = 0; z0 < A.lz; z0 += kPlaneZ) {
+        const int nz = min(kPlaneZ, A.lz - z0);
+        __syncthreads();
+        for (int e = threadIdx.x; e < NM * nz; e += 256) {
+            const int k = e / nz, z = e - k * nz;
+            const long q = k < A.n ? ((long)A.mz[k] * (z0 + z)) % A.lz : 0;
+            sincospi(-2.0 * (double)((q + A.lz) % A.lz) / A.lz, &ph[k][z].y, &ph[k][z].x);
+        }
+        __syncthreads();
+        if (!live) continue;
+#pragma unroll 2
+        for (int z = 0; z < nz; ++z) {
+            const double2 v = A.S[(size_t)(z0 + z) * per + idx];
+#pragma unroll
+            for (int k = 0; k < NM; ++k) {
+                const double2 f = ph[k][z];
+                const double a = f.x * v.x, b = f.y * v.y, c = f.x * v.y, e = f.y * v.x;
+                s[k].x += a - b;
+                s[k].y += c + e;
+                d[k].x += a + b;
+                d[k].y += c - e;
+            }
+        }
+    }
+    if (!live) return;
+    const long mirror = idx + (long)(m - l) * (nev - 1);   // (t, m, l)
+#pragma unroll
+    for (int k = 0; k < NM; ++k) {
+        if (k >= A.n) break;
+        double2 *o = A.phi + (size_t)A.out[k] * per;
+        if (!A.flip[k]) o[idx] = s[k];
+        if (A.flip[k] || (A.herm && (l >> 4) < (m >> 4))) o[mirror] = make_double2(d[k].x, -d[k].y);
+    }
 }
 
 void contract_shape(const Ctx &c, int kind, int nev, int nmom, ContractArgs &a) {
@@ -328,7 +441,8 @@ void contract_shape(const Ctx &c, int kind, int nev, int nmom, ContractArgs &a) 
     a.lt = c.g.lt;
     a.vs = c.g.lx * c.g.ly * c.g.lz;
     a.nev = nev;
-    a.ncol = kind == 0 ? nev : nev * (nev - 1) / 2;
+    a.ncol = kind == 0 ? nev : PairTable(nev).ncol();
+    a.plane = a.herm = 0;
     const int cols = kind == 0 ? 64 : 128;
     a.ntile = std::max(1, (a.ncol + cols - 1) / cols);
     a.nmom = nmom;
@@ -346,12 +460,100 @@ static size_t group_bytes(const Ctx &c, int kind, int nev, int nmom) {
     return round256((size_t)a.nsplit * a.nmom * a.lt * nev * a.ncol * 16);
 }
 
+// S(z) of one group of doublets
+static size_t planes_bytes(const Ctx &c, int nev) { return round256((size_t)c.g.lz * c.g.lt * nev * nev * 16); }
+
 size_t contract_workspace_bytes(const Ctx &c, int kind, int nev, int n_mom) {
     if (nev < 1 || nev > kCRows || n_mom < 1 || (kind != 0 && kind != 1)) return 0;
     // the largest launch group: a full one, or the last (its K split may be finer)
     size_t b = group_bytes(c, kind, nev, std::min(n_mom, kCMaxMom));
     if (n_mom > kCMaxMom && n_mom % kCMaxMom) b = std::max(b, group_bytes(c, kind, nev, n_mom % kCMaxMom));
+    if (kind == 0) {
+        b = std::max(b, planes_bytes(c, nev));
+        // what is left after some momenta went by planes may be split finer
+        for (int n = 1; n < std::min(n_mom, kCMaxMom); ++n) b = std::max(b, group_bytes(c, kind, nev, n));
+    }
     return b;
+}
+
+// The momenta of one (px, py), up to an overall sign.
+struct PlaneGroup {
+    int px, py, herm;
+    std::vector<int> members, flip;
+};
+
+// Doublets by planes pay when the products they save outweigh the extra launches (about
+// 10 us) and the pass over S(z): a plane of 64 sites costs as much as writing and reading
+// its S(z) five times, and one momentum's products run at about 50 TFLOP/s.
+static bool planes_pay(const Ctx &c, int nev, const PlaneGroup &g) {
+    if (c.g.lx * c.g.ly < 64) return false;
+    const double saved = (double)g.members.size() - (g.herm ? 0.625 : 1.0);
+    const double one = 8.0 * 6.0 * c.g.vh * nev * nev / 50e12;   // seconds per momentum
+    return saved * one > 40e-6;
+}
+
+static std::vector<PlaneGroup> plane_groups(const Ctx &c, int n_mom, const int *mom) {
+    std::vector<PlaneGroup> gs;
+    auto red = [](int v, int l) { return (v % l + l) % l; };
+    const int lx = c.g.lx, ly = c.g.ly;
+    for (int q = 0; q < n_mom; ++q) {
+        const int px = red(mom[3 * q], lx), py = red(mom[3 * q + 1], ly);
+        const int nx = red(-px, lx), ny = red(-py, ly);
+        size_t k = 0;
+        int flip = 0;
+        for (; k < gs.size(); ++k) {
+            if (gs[k].px == px && gs[k].py == py) break;
+            if (gs[k].px == nx && gs[k].py == ny) {
+                flip = 1;
+                break;
+            }
+        }
+        if (k == gs.size()) gs.push_back({px, py, px == nx && py == ny ? 1 : 0, {}, {}});
+        gs[k].members.push_back(q);
+        gs[k].flip.push_back(flip);
+    }
+    return gs;
+}
+
+// Phi of one group's momenta through its S(z)
+static laph_status doublet_planes(const Ctx &c, const PlaneGroup &g, double *out, const double *V, int nev,
+                                  const int *mom, char *work) {
+    ContractArgs a;
+    contract_shape(c, 0, nev, 1, a);
+    a.plane = a.lx * a.ly;
+    a.herm = g.herm;
+    a.nsplit = a.lz;
+    a.nchunk = (a.plane + kCS - 1) / kCS;
+    a.mom[0] = g.px;
+    a.mom[1] = g.py;
+    a.mom[2] = 0;
+    a.V = reinterpret_cast<const double2 *>(V);
+    a.scratch = reinterpret_cast<double2 *>(work);
+    hipLaunchKernelGGL((contract_kernel<0, 1>), dim3((unsigned)(a.lt * a.lz)), dim3(kCB), 0, c.stream, a);
+    LAPH_TRY(check_launch("contract_kernel"));
+    for (size_t m0 = 0; m0 < g.members.size(); m0 += kPlaneMom) {
+        PlaneArgs p;
+        p.lt = a.lt;
+        p.lz = a.lz;
+        p.nev = nev;
+        p.herm = g.herm;
+        p.n = (int)std::min<size_t>(kPlaneMom, g.members.size() - m0);
+        for (int k = 0; k < kPlaneMom; ++k) {
+            const bool on = k < p.n;
+            p.mz[k] = on ? mom[3 * g.members[m0 + k] + 2] % a.lz : 0;
+            p.flip[k] = on ? g.flip[m0 + k] : 0;
+            p.out[k] = on ? g.members[m0 + k] : 0;
+        }
+        p.S = a.scratch;
+        p.phi = reinterpret_cast<double2 *>(out);
+        const unsigned nb = (unsigned)(((long)a.lt * nev * nev + 255) / 256);
+        if (p.n <= 2)
+            hipLaunchKernelGGL(doublet_planes_kernel<2>, dim3(nb), dim3(256), 0, c.stream, p);
+        else
+            hipLaunchKernelGGL(doublet_planes_kernel<kPlaneMom>, dim3(nb), dim3(256), 0, c.stream, p);
+        LAPH_TRY(check_launch("doublet_planes_kernel"));
+    }
+    return LAPH_OK;
 }
 
 laph_status contract(const Ctx &c, int kind, double *out, const double *V, int nev, int n_mom, const int *mom_host,
@@ -362,12 +564,28 @@ laph_status contract(const Ctx &c, int kind, double *out, const double *V, int n
     const size_t need = contract_workspace_bytes(c, kind, nev, n_mom);
     if (!work || bytes < need) return set_error(LAPH_ERR_WORKSPACE, "workspace too small: %zu < %zu", bytes, need);
     const size_t per = (size_t)c.g.lt * nev * nev * (kind == 0 ? 1 : nev);
-    for (int p0 = 0; p0 < n_mom; p0 += kCMaxMom) {
-        const int np = std::min(kCMaxMom, n_mom - p0);
+    // momenta left for the launches that carry the whole phase: all, or those whose (px, py)
+    // does not pay by planes
+    std::vector<int> rest;
+    if (kind == 0) {
+        for (const PlaneGroup &g : plane_groups(c, n_mom, mom_host)) {
+            if (planes_pay(c, nev, g))
+                LAPH_TRY(doublet_planes(c, g, out, V, nev, mom_host, work));
+            else
+                rest.insert(rest.end(), g.members.begin(), g.members.end());
+        }
+    } else {
+        for (int q = 0; q < n_mom; ++q) rest.push_back(q);
+    }
+    for (size_t p0 = 0; p0 < rest.size(); p0 += kCMaxMom) {
+        const int np = (int)std::min<size_t>(kCMaxMom, rest.size() - p0);
         ContractArgs a;
         contract_shape(c, kind, nev, np, a);
         if (group_bytes(c, kind, nev, np) > bytes) return set_error(LAPH_ERR_WORKSPACE, "workspace too small");
-        for (int q = 0; q < 3 * np; ++q) a.mom[q] = mom_host[3 * p0 + q];
+        for (int q = 0; q < np; ++q) {
+            a.out[q] = rest[p0 + q];
+            for (int k = 0; k < 3; ++k) a.mom[3 * q + k] = mom_host[3 * rest[p0 + q] + k];
+        }
         a.V = reinterpret_cast<const double2 *>(V);
         a.scratch = reinterpret_cast<double2 *>(work);
         const unsigned nblk = (unsigned)(a.lt * a.nsplit * a.ntile * a.nmom);
@@ -380,10 +598,10 @@ laph_status contract(const Ctx &c, int kind, double *out, const double *V, int n
         const unsigned rb = (unsigned)((total + 255) / 256);
         if (kind == 0)
             hipLaunchKernelGGL(doublet_reduce_kernel, dim3(rb), dim3(256), 0, c.stream, a,
-                               reinterpret_cast<double2 *>(out), p0, n_mom);
+                               reinterpret_cast<double2 *>(out));
         else
             hipLaunchKernelGGL(triplet_reduce_kernel, dim3(rb), dim3(256), 0, c.stream, a,
-                               reinterpret_cast<double2 *>(out), p0);
+                               reinterpret_cast<double2 *>(out));
         LAPH_TRY(check_launch("contract_reduce_kernel"));
     }
     return LAPH_OK;
