@@ -38,15 +38,15 @@ __device__ __forceinline__ void reduce_store(double *v, int nv, double *dst, siz
 // Entries of the slot list this launch walks: the flagged list (built on the
 // device after the rho finalize) in flagged mode, the slot list otherwise.
 __device__ __forceinline__ int blas_count(const BlasArgs &A, int mode) {
-    return mode == kModeFlagged ? *A.nflist : *A.nlist;
+    return mode >= kModeFlagged ? *A.nflist : *A.nlist;
 }
 
 // slot of list entry j, or -1 if it has nothing to do in this mode
 __device__ __forceinline__ int blas_slot_at(const BlasArgs &A, int mode, int j) {
-    const int s = mode == kModeFlagged ? A.flist[j] : A.list[j];
+    const int s = mode >= kModeFlagged ? A.flist[j] : A.list[j];
     const SlotState &st = A.st[s];
-    if (mode == kModeActive && st.status != LAPH_RHS_ACTIVE) return -1;
-    if (mode == kModeFlagged && !(st.status == LAPH_RHS_ACTIVE && st.flag != 0)) return -1;
+    if (mode != kModeAll && st.status != LAPH_RHS_ACTIVE) return -1;
+    if (mode == kModeFlagged && st.flag == 0) return -1;
     return s;
 }
 
@@ -68,15 +68,16 @@ __device__ __forceinline__ int first_site(const BlasArgs &A) {
     return b * kB;
 }
 
-// p = r + beta (p - omega v);  beta == 0 means p = r (fresh start: p, v not read).
+// p = r + beta (p - omega v) of the active slots, or of those that took a reliable update (where
+// the others' p is updated with their x and r);  beta == 0 means p = r (fresh start: p, v not read).
 // Sites outside A.win are not touched; outside A.win_pv p and v are zero and not read.
 template <class P>
-__global__ __launch_bounds__(kB) void p_update_kernel(BlasArgs A) {
+__global__ __launch_bounds__(kB) void p_update_kernel(BlasArgs A, int mode) {
     using R = typename P::real;
     const int h = first_site(A) + threadIdx.x;
     if (h >= A.vh || !in_window(A.win, h, A.vh)) return;
     const bool zero_pv = !in_window(A.win_pv, h, A.vh);
-    LAPH_FOR_SLOTS(A, kModeActive, s) {
+    LAPH_FOR_SLOTS(A, mode, s) {
         const double2 beta = A.st[s].beta;
         cplx<R> r[12];
         SpinorIO<P>::load(A.r.at(s), A.vh, h, r);
@@ -112,33 +113,22 @@ __global__ __launch_bounds__(kB) void s_update_kernel(BlasArgs A) {
 }
 
 // x_lo += alpha p + omega s (x_lo = ... after a fold or at the start);  r = s - omega t;
-// partials <r^, r>, |r|^2.  Outside A.win p, s and t are zero: nothing to do there, except
-// that an x_lo marked zero becomes zero in memory.  r^ is not read where it is zero.
+// partials <r^, r>, |r|^2
 template <class P, class PX>
 __global__ __launch_bounds__(kB) void xr_update_kernel(BlasArgs A) {
     using R = typename P::real;
     using RX = typename PX::real;
-    const int h0 = blockIdx.x * kB, h = h0 + threadIdx.x;
-    const bool outside = block_outside(A.win, h0, min(kB, A.vh - h0), A.vh);   // uniform
-    const bool live = h < A.vh && in_window(A.win, h, A.vh);
-    const bool rh_zero = block_outside(A.win_rh, h0, min(kB, A.vh - h0), A.vh) && *A.rh_full == 0;
+    const int h = blockIdx.x * kB + threadIdx.x;
     LAPH_FOR_SLOTS(A, kModeActive, s) {
-        if (!live && h < A.vh && A.st[s].xlo_zero) {
-            cplx<RX> x[12];
-#pragma unroll
-            for (int c = 0; c < 12; ++c) x[c] = {RX(0), RX(0)};
-            SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
-        }
-        if (outside) continue;
         double part[3] = {0, 0, 0};
-        if (live) {
+        if (h < A.vh) {
             const cplx<R> al = c_of<R>(A.st[s].alpha), om = c_of<R>(A.st[s].omega);
             cplx<R> p[12], r[12], t[12], rh[12];
             cplx<RX> x[12];
             SpinorIO<P>::load(A.p.at(s), A.vh, h, p);
             SpinorIO<P>::load(A.r.at(s), A.vh, h, r);
             SpinorIO<P>::load(A.t.at(s), A.vh, h, t);
-            if (A.st[s].xlo_zero) {
+            if (A.st[s].iters < A.st[s].xlo_from) {   // (iters counts this iteration after this kernel)
 #pragma unroll
                 for (int c = 0; c < 12; ++c) x[c] = {RX(0), RX(0)};
             } else {
@@ -152,32 +142,93 @@ __global__ __launch_bounds__(kB) void xr_update_kernel(BlasArgs A) {
             }
             SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
             SpinorIO<P>::store(A.r.at(s), A.vh, h, r);
+            SpinorIO<P>::load(A.rh.at(s), A.vh, h, rh);
             cplx<R> d = {R(0), R(0)};
             R n2 = R(0);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) n2 += r[c].re * r[c].re + r[c].im * r[c].im;
-            if (!rh_zero) {
-                SpinorIO<P>::load(A.rh.at(s), A.vh, h, rh);
-#pragma unroll
-                for (int c = 0; c < 12; ++c) cmac_conj(d, rh[c], r[c]);
+            for (int c = 0; c < 12; ++c) {
+                cmac_conj(d, rh[c], r[c]);
+                n2 += r[c].re * r[c].re + r[c].im * r[c].im;
             }
             part[0] = d.re;
             part[1] = d.im;
             part[2] = n2;
         }
-        reduce_store(part, 3, A.partials + (size_t)s * 3 * A.pstride + blockIdx.x, A.pstride);
+        reduce_store(part, 3, A.partials + (size_t)s * kSolverPq * A.pstride + blockIdx.x, A.pstride);
+    }
+}
+
+// The same with r^ confined to the source's window, and in the same pass,
+// unless a reliable update is about to replace r, p = r + beta (p - omega v).  One pass
+// reads p, s, t, v and x_lo once (504 bytes per site and RHS in FP16N); beta is known
+// before it because rho = <r^, r> = <r^, s> - omega <r^, t> and |r|^2 = |s|^2 - |<t, s>|^2 / |t|^2 come from the sums of the stage that formed t, which reads r^
+// in its window only.  (<r^, s> vanishes by alpha up to rounding; taking it as zero let rho drift
+// from <r^, r>: about one FP16N solve in 400 stalled.  Without a window that stage would read all of r^ for a saving of 2
+// vectors of 23, so other solves keep the two kernels and the direct sums.)
+// Outside A.win p, s and t are zero: nothing to do there, except that an x_lo not written
+// since the last fold becomes zero in memory; outside A.win_pv p and v are zero, not read.
+template <class P, class PX>
+__global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(sizeof(typename P::real) == 4 ? 4 : 2))) void
+xrp_update_kernel(BlasArgs A) {
+    using R = typename P::real;
+    using RX = typename PX::real;
+    const int h = first_site(A) + threadIdx.x;
+    if (h >= A.vh) return;
+    const bool live = in_window(A.win, h, A.vh);
+    const bool zero_pv = !in_window(A.win_pv, h, A.vh);
+    LAPH_FOR_SLOTS(A, kModeActive, s) {
+        const bool fresh_x = A.st[s].iters == A.st[s].xlo_from;
+        if (!live) {
+            if (fresh_x) {
+                cplx<RX> x[12];
+#pragma unroll
+                for (int c = 0; c < 12; ++c) x[c] = {RX(0), RX(0)};
+                SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
+            }
+            continue;
+        }
+        const cplx<R> al = c_of<R>(A.st[s].alpha), om = c_of<R>(A.st[s].omega), be = c_of<R>(A.st[s].beta);
+        cplx<R> p[12], r[12], t[12];
+        SpinorIO<P>::load(A.p.at(s), A.vh, h, p);
+        SpinorIO<P>::load(A.r.at(s), A.vh, h, r);
+        SpinorIO<P>::load(A.t.at(s), A.vh, h, t);
+        {
+            cplx<RX> x[12];
+            if (fresh_x) {
+#pragma unroll
+                for (int c = 0; c < 12; ++c) x[c] = {RX(0), RX(0)};
+            } else {
+                SpinorIO<PX>::load(A.x.at(s), A.vh, h, x);
+            }
+#pragma unroll
+            for (int c = 0; c < 12; ++c) {
+                const cplx<R> dx = al * p[c] + om * r[c];
+                x[c] = x[c] + cplx<RX>{RX(dx.re), RX(dx.im)};
+            }
+            SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
+        }
+#pragma unroll
+        for (int c = 0; c < 12; ++c) r[c] = r[c] - om * t[c];
+        SpinorIO<P>::store(A.r.at(s), A.vh, h, r);
+        if (A.st[s].flag != 0) continue;
+        if (!zero_pv) {
+            SpinorIO<P>::load(A.v.at(s), A.vh, h, t);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) r[c] = r[c] + be * (p[c] - om * t[c]);
+        }
+        SpinorIO<P>::store(A.p.at(s), A.vh, h, r);
     }
 }
 
 // reliable update, part 1: x64 += x_lo (flagged slots).  x_lo is not cleared here: the
-// update's finalize marks it zero (xlo_zero) and the next x/r update overwrites it.
+// update's finalize says which iteration writes it next (xlo_from), without reading it.
 template <class PX>
 __global__ __launch_bounds__(kB) void accumulate_kernel(BlasArgs A, int mode) {
     using RX = typename PX::real;
     const int h = blockIdx.x * kB + threadIdx.x;
     if (h >= A.vh) return;
     LAPH_FOR_SLOTS(A, mode, s) {
-        if (A.st[s].xlo_zero) continue;   // uniform: nothing to fold
+        if (A.st[s].iters < A.st[s].xlo_from) continue;   // uniform: nothing to fold
         cplx<RX> x[12];
         cplx<double> y[12];
         SpinorIO<PX>::load(A.x.at(s), A.vh, h, x);
@@ -188,8 +239,8 @@ __global__ __launch_bounds__(kB) void accumulate_kernel(BlasArgs A, int mode) {
     }
 }
 
-// r = lo(r64); restart (flag 2) or init: r^ = r (the init finalize marks x_lo zero).  init 1: r
-// lives on the source's window, 2: on the whole lattice.
+// r = lo(r64); restart (flag 2) or init: r^ = r; init: p = r.  init 1: r lives on the source's
+// window, 2: on the whole lattice.
 // partials <r^, r>, |r|^2
 template <class P, class PX>
 __global__ __launch_bounds__(kB) void lower_kernel(BlasArgs A, int mode, int init) {
@@ -209,6 +260,7 @@ __global__ __launch_bounds__(kB) void lower_kernel(BlasArgs A, int mode, int ini
             // work with the stored (rounded) values so r^ and r agree exactly
             SpinorIO<P>::load(A.r.at(s), A.vh, h, r);
             const bool reset = init || A.st[s].flag == 2;
+            if (init) SpinorIO<P>::store(A.p.at(s), A.vh, h, r);
             if (reset) {
                 SpinorIO<P>::store(A.rh.at(s), A.vh, h, r);
                 SpinorIO<P>::load(A.rh.at(s), A.vh, h, rh);
@@ -226,7 +278,8 @@ __global__ __launch_bounds__(kB) void lower_kernel(BlasArgs A, int mode, int ini
             part[1] = d.im;
             part[2] = n2;
         }
-        reduce_store(part, 3, A.partials + (size_t)s * 3 * A.pstride + blockIdx.x, A.pstride);
+        // quantities 3 .. 5: those before them hold the update's |r64|^2
+        reduce_store(part, 3, A.partials + ((size_t)s * kSolverPq + 3) * A.pstride + blockIdx.x, A.pstride);
     }
 }
 
@@ -250,7 +303,7 @@ __global__ __launch_bounds__(kB) void norm2_kernel(BlasArgs A, Operand v1, Opera
             }
             part[0] = n2;
         }
-        reduce_store(part, 1, A.partials + (size_t)s * 3 * A.pstride + blockIdx.x, A.pstride);
+        reduce_store(part, 1, A.partials + (size_t)s * kSolverPq * A.pstride + blockIdx.x, A.pstride);
     }
 }
 
@@ -271,68 +324,76 @@ __global__ __launch_bounds__(kB) void copy64_kernel(BlasArgs A, Operand dst, Ope
     }
 }
 
-// Flagged slots after the rho finalize: the list of slots that take a reliable
-// update this iteration, and FP64 register tiles of them (tiles never mix
-// masses).  One block; entries of the static FP64 tile table (already grouped
-// by mass) are tested in parallel, then packed in table order by one thread.
-__global__ __launch_bounds__(kB) void flag_tiles_kernel(FlagArgs A) {
-    __shared__ int ks[kB], km[kB];
-    const int total = *A.ntiles * A.nr;
-    int cur = -1, fill = 0, cm = -1, nf = 0;   // packing state (thread 0)
-    for (int base = 0; base < total; base += kB) {
+// Flagged slots after an iteration's last finalize: the list of slots that take a reliable update this
+// iteration, and FP64 tiles of them (tiles never mix masses).  One workgroup; entries of
+// the static FP64 tile table (already grouped by mass) are tested in parallel, then packed in
+// table order by one lane.  The flags were written by workgroups of this launch: read past the
+// caches.
+__device__ void flag_tiles(const FinArgs &A) {
+    __shared__ int ks[512], km[512];
+    const int nth = blockDim.x;
+    const FlagArgs &F = A.flags;
+    const int total = *F.ntiles * F.nr;
+    int cur = -1, fill = 0, cm = -1, nf = 0;   // packing state (lane 0)
+    for (int base = 0; base < total; base += nth) {
         const int e = base + (int)threadIdx.x;
         int s = -1, m = 0;
         if (e < total) {
-            s = A.tile_slots[e];
-            m = A.tile_mass[e / A.nr];
-            if (s >= 0 && !(A.st[s].status == LAPH_RHS_ACTIVE && A.st[s].flag != 0)) s = -1;
+            s = F.tile_slots[e];
+            m = F.tile_mass[e / F.nr];
+            if (s >= 0) {
+                const int status = __hip_atomic_load(&A.st[s].status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int flag = __hip_atomic_load(&A.st[s].flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!(status == LAPH_RHS_ACTIVE && flag != 0)) s = -1;
+            }
         }
         ks[threadIdx.x] = s;
         km[threadIdx.x] = m;
         __syncthreads();
         if (threadIdx.x == 0) {
-            const int n = min(kB, total - base);
+            const int n = min(nth, total - base);
             for (int i = 0; i < n; ++i) {
                 const int si = ks[i];
                 if (si < 0) continue;
-                if (cur < 0 || fill == A.nr || km[i] != cm) {
+                if (cur < 0 || fill == F.nr || km[i] != cm) {
                     ++cur;
-                    for (int k = 0; k < A.nr; ++k) A.out_slots[cur * A.nr + k] = -1;
-                    A.out_mass[cur] = km[i];
+                    for (int k = 0; k < F.nr; ++k) F.out_slots[cur * F.nr + k] = -1;
+                    F.out_mass[cur] = km[i];
                     cm = km[i];
                     fill = 0;
                 }
-                A.out_slots[cur * A.nr + fill++] = si;
-                A.flist[nf++] = si;
+                F.out_slots[cur * F.nr + fill++] = si;
+                F.flist[nf++] = si;
             }
         }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        *A.out_ntiles = cur + 1;
-        *A.nflist = nf;
+        *F.out_ntiles = cur + 1;
+        *F.nflist = nf;
     }
 }
 
 // ---------------------------------------------------------------------------
-// finalize kernels: one 64-thread wave per slot sums the partials in fixed order
+// finalize kernels: one workgroup per slot, one 64-thread wave per quantity sums the
+// partials in fixed order
 // ---------------------------------------------------------------------------
 // Eight independent loads in flight per lane: the partials were just written by
 // workgroups on every XCD, and a loop that waits for each load in turn spends ~0.1 ms
 // of latency per slot and quantity.  The summation order is still fixed.
 // A windowed producer wrote only A.count blocks from A.first on (cyclic).
-__device__ __forceinline__ double wave_sum_partials(const double *p, const FinArgs &A) {
+__device__ __forceinline__ double wave_sum_partials(const double *p, int first, int count, int nsb) {
     double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     auto at = [&](int i) {
-        const int b = A.first + i;
-        return p[b < A.nsb ? b : b - A.nsb];
+        const int b = first + i;
+        return p[b < nsb ? b : b - nsb];
     };
-    int i = threadIdx.x;
-    for (; i + 7 * 64 < A.count; i += 8 * 64) {
+    int i = threadIdx.x & 63;
+    for (; i + 7 * 64 < count; i += 8 * 64) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) a[k] += at(i + 64 * k);
     }
-    for (; i < A.count; i += 64) a[0] += at(i);
+    for (; i < count; i += 64) a[0] += at(i);
     double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
@@ -349,18 +410,63 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
 __device__ __forceinline__ bool finite2(double2 a) { return isfinite(a.x) && isfinite(a.y); }
 __device__ __forceinline__ double cabs2(double2 a) { return a.x * a.x + a.y * a.y; }
 
-__global__ void finalize_kernel(FinArgs A, int what) {
+// end of an iteration: beta from rho_new = rn, and whether a reliable update is due (r2 = |r|^2;
+// finite: a norm that shows NaN and infinities)
+__device__ __forceinline__ void finalize_rho(SlotState &st, double2 rn, double r2, double finite) {
+    st.iters += 1;
+    st.r2 = r2;
+    if (!isfinite(finite) || !finite2(rn)) st.flag = 2;
+    if (st.flag != 2) {
+        if (cabs2(st.omega) == 0.0 || cabs2(st.rho) == 0.0 || cabs2(rn) == 0.0) {
+            st.flag = 2;
+        } else {
+            st.beta = cmul(cdiv(rn, st.rho), cdiv(st.alpha, st.omega));
+        }
+    }
+    st.rho_prev = st.rho;
+    st.rho = rn;
+    if (r2 <= st.stop2 || r2 < st.delta2 * st.r2_upd || st.iters >= st.maxiter) st.flag |= 1;
+}
+
+// rho, beta and the residual norm after r was replaced by the FP64 residual (or at the start)
+__device__ __forceinline__ void finalize_residual(SlotState &st, double2 rn, double r2, bool restart) {
+    st.r2 = r2;
+    if (restart) {
+        st.beta = make_double2(0, 0);
+        st.rho_prev = make_double2(1, 0);
+        st.alpha = make_double2(1, 0);
+        st.omega = make_double2(1, 0);
+    } else {
+        st.beta = cmul(cdiv(rn, st.rho_prev), cdiv(st.alpha, st.omega));
+    }
+    st.rho = rn;
+    st.flag = 0;
+}
+
+__device__ __forceinline__ void finalize_slot(const FinArgs &A, int what) {
     const int j = blockIdx.x;
     if (j >= *A.nlist) return;
     const int s = A.list[j];
     SlotState &st = A.st[s];
-    const double *P = A.partials + (size_t)s * 3 * A.pstride;
+    const double *P = A.partials + (size_t)s * kSolverPq * A.pstride;
     const bool active = st.status == LAPH_RHS_ACTIVE;
+    // wave w sums quantity q0 + w (an update's last three: blocks of another kernel) for thread 0
+    __shared__ double v[8];
+    auto sums = [&](int q0) {
+        const int w = threadIdx.x >> 6;
+        const bool low = what == kFinUpdate && w > 0;
+        const int q = low ? 2 + w : q0 + w;
+        const double *p = P + (size_t)q * A.pstride;
+        const double t = low ? wave_sum_partials(p, 0, A.nsb2, A.nsb2) : wave_sum_partials(p, A.first, A.count, A.nsb);
+        if ((threadIdx.x & 63) == 0) v[w] = t;
+        __syncthreads();
+    };
     switch (what) {
         case kFinAlpha: {  // sigma = <r^, v>; alpha = rho / sigma
             if (!active) return;
-            const double2 sig = make_double2(wave_sum_partials(P, A), wave_sum_partials(P + A.pstride, A));
+            sums(0);
             if (threadIdx.x) return;
+            const double2 sig = make_double2(v[0], v[1]);
             if (!finite2(sig) || cabs2(sig) <= 1e-300 * (cabs2(st.rho) + 1e-300) || cabs2(sig) == 0.0) {
                 st.alpha = make_double2(0, 0);
                 st.flag = 2;
@@ -371,9 +477,10 @@ __global__ void finalize_kernel(FinArgs A, int what) {
         }
         case kFinOmega: {  // omega = <t, s> / |t|^2
             if (!active) return;
-            const double2 ts = make_double2(wave_sum_partials(P, A), wave_sum_partials(P + A.pstride, A));
-            const double tt = wave_sum_partials(P + 2 * A.pstride, A);
+            sums(0);
             if (threadIdx.x) return;
+            const double2 ts = make_double2(v[0], v[1]);
+            const double tt = v[2];
             if (!(tt > 0) || !isfinite(tt) || !finite2(ts)) {
                 st.omega = make_double2(0, 0);
                 st.flag = 2;
@@ -382,37 +489,48 @@ __global__ void finalize_kernel(FinArgs A, int what) {
             }
             return;
         }
-        case kFinRho: {  // rho_new = <r^, r>, r2 = |r|^2; beta; decide on a reliable update
+        case kFinRho: {  // rho = <r^, r>, |r|^2; beta; whether a reliable update is due
             if (!active) return;
-            const double2 rn = make_double2(wave_sum_partials(P, A), wave_sum_partials(P + A.pstride, A));
-            const double r2 = wave_sum_partials(P + 2 * A.pstride, A);
+            sums(0);
             if (threadIdx.x) return;
-            st.iters += 1;
-            st.r2 = r2;
-            if (!isfinite(r2) || !finite2(rn)) st.flag = 2;
-            if (st.flag != 2) {
-                if (cabs2(st.omega) == 0.0 || cabs2(st.rho) == 0.0 || cabs2(rn) == 0.0) {
-                    st.flag = 2;
-                } else {
-                    st.beta = cmul(cdiv(rn, st.rho), cdiv(st.alpha, st.omega));
-                }
-            }
-            st.rho_prev = st.rho;
-            st.rho = rn;
-            st.xlo_zero = 0;   // the x/r update just wrote x_lo
-            if (r2 <= st.stop2 || r2 < st.delta2 * st.r2_upd || st.iters >= st.maxiter) st.flag |= 1;
+            finalize_rho(st, make_double2(v[0], v[1]), v[2], v[2]);
             return;
         }
-        case kFinUpdate: {  // r2_upd = |b_hat - M x64|^2 after a reliable update
-            if (!(active && st.flag != 0)) return;
-            const double r2 = wave_sum_partials(P, A);
+        case kFinOmegaRho: {
+            // omega = <t, s> / |t|^2 and what r = s - omega t will have: rho = <r^, s> - omega <r^, t>,
+            // |r|^2 = |s|^2 - |<t, s>|^2 / |t|^2; beta; whether a reliable update is due
+            if (!active) return;
+            sums(0);
             if (threadIdx.x) return;
+            const double2 ts = make_double2(v[0], v[1]), rt = make_double2(v[4], v[5]);
+            const double tt = v[2];
+            double2 rn = make_double2(0, 0);
+            double r2 = v[3];
+            if (!(tt > 0) || !isfinite(tt) || !finite2(ts)) {
+                st.omega = make_double2(0, 0);
+                st.flag = 2;
+            } else {
+                st.omega = make_double2(ts.x / tt, ts.y / tt);
+                const double2 wt = cmul(st.omega, rt);
+                rn = make_double2(v[6] - wt.x, v[7] - wt.y);
+                r2 = fmax(0.0, v[3] - cabs2(ts) / tt);
+            }
+            finalize_rho(st, rn, r2, v[3]);
+            return;
+        }
+        case kFinUpdate: {
+            // after a reliable update: r2_upd = |b_hat - M x64|^2, whether the slot is done, and rho and
+            // beta from the corrected residual r = lo(r64)
+            if (!(active && st.flag != 0)) return;
+            sums(0);
+            if (threadIdx.x) return;
+            const double u2 = v[0];
             st.updates += 1;
-            st.r2_upd = r2;
-            st.xlo_zero = 1;   // folded into x64 by this update (accumulate, or the FP64 stage forming r64)
-            if (!isfinite(r2)) {
+            st.r2_upd = u2;
+            st.xlo_from = st.iters + 1;   // folded into x64 by this update (accumulate, or the FP64 stage forming r64)
+            if (!isfinite(u2)) {
                 st.status = LAPH_RHS_NONFINITE;
-            } else if (r2 <= st.stop2) {
+            } else if (u2 <= st.stop2) {
                 st.status = LAPH_RHS_CONVERGED;
             } else if (st.iters >= st.maxiter) {
                 st.status = LAPH_RHS_NOCONV;
@@ -420,52 +538,58 @@ __global__ void finalize_kernel(FinArgs A, int what) {
                 st.restarts += 1;
                 if (st.restarts > A.max_restarts) st.status = LAPH_RHS_BREAKDOWN;
             }
+            if (st.status != LAPH_RHS_ACTIVE) return;
+            finalize_residual(st, make_double2(v[1], v[2]), v[3], st.flag == 2);
             return;
         }
-        case kFinRho2:    // after r = lo(r64): rho and beta from the corrected residual
         case kFinInit: {  // first residual of a solve
-            const bool init = what == kFinInit;
-            if (!(active && (init || st.flag != 0))) return;
-            const double2 rn = make_double2(wave_sum_partials(P, A), wave_sum_partials(P + A.pstride, A));
-            const double r2 = wave_sum_partials(P + 2 * A.pstride, A);
+            if (!active) return;
+            sums(3);
             if (threadIdx.x) return;
-            st.r2 = r2;
-            if (init || st.flag == 2) {
-                st.beta = make_double2(0, 0);
-                st.rho_prev = make_double2(1, 0);
-                st.alpha = make_double2(1, 0);
-                st.omega = make_double2(1, 0);
-            } else {
-                st.beta = cmul(cdiv(rn, st.rho_prev), cdiv(st.alpha, st.omega));
-            }
-            st.rho = rn;
-            st.flag = 0;
-            if (init) st.xlo_zero = 1;
+            finalize_residual(st, make_double2(v[0], v[1]), v[2], true);
+            st.xlo_from = st.iters + 1;
             return;
         }
         case kFinBnorm: {  // |B|^2 of the full-lattice source; zero or non-finite sources end here
-            const double b2 = wave_sum_partials(P, A);
+            sums(0);
             if (threadIdx.x) return;
+            const double b2 = v[0];
             st.bnorm2 = b2;
             if (!isfinite(b2)) st.status = LAPH_RHS_NONFINITE;
             return;
         }
         case kFinR64: {  // |r64|^2 at the start of a solve pass
             if (!active) return;
-            const double r2 = wave_sum_partials(P, A);
+            sums(0);
             if (threadIdx.x) return;
+            const double r2 = v[0];
             st.r2_upd = r2;
             if (!isfinite(r2)) st.status = LAPH_RHS_NONFINITE;
             else if (r2 <= st.stop2) st.status = LAPH_RHS_CONVERGED;
             return;
         }
         case kFinTrueRes: {  // accumulate |B - D X|^2 (called for the even and the odd part)
-            const double r2 = wave_sum_partials(P, A);
+            sums(0);
             if (threadIdx.x) return;
+            const double r2 = v[0];
             st.true_res2 += r2;
             return;
         }
     }
+}
+
+__global__ __launch_bounds__(512) void finalize_kernel(FinArgs A, int what) {
+    finalize_slot(A, what);
+    if (what != kFinRho && what != kFinOmegaRho) return;
+    // the workgroup that finishes last compacts the slots flagged for a reliable update
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        const int n = __hip_atomic_fetch_add(A.flags.done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        last = n == (int)gridDim.x - 1;
+        if (last) __hip_atomic_store(A.flags.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (last) flag_tiles(A);
 }
 
 // ---------------------------------------------------------------------------
@@ -478,11 +602,19 @@ static laph_status dispatch_prec(int prec, F &&f) {
     return f(F16N{}, F32{});
 }
 
-laph_status blas_p_update(const Ctx &c, const BlasArgs &a, int prec) {
+// grid rows: one per list entry, or a quarter of them in flagged mode (a block
+// then walks several flagged slots; the flagged count is known only on the device)
+static dim3 blas_grid(const BlasArgs &a, int mode) {
+    const int rows = mode == kModeFlagged ? (a.nlist_max + 3) / 4 : a.nlist_max;
+    return dim3(a.nsb, rows > 0 ? rows : 1);
+}
+
+laph_status blas_p_update(const Ctx &c, const BlasArgs &a, int prec, int mode) {
     BlasArgs w = a;
-    dim3 grid(window_blocks(a.win, kB, a.nsb, a.vh, &w.sb_first), a.nlist_max);
+    dim3 grid = blas_grid(a, mode == kModeUpdated ? kModeFlagged : mode);
+    grid.x = window_blocks(a.win, kB, a.nsb, a.vh, &w.sb_first);
     return dispatch_prec(prec, [&](auto P, auto) {
-        hipLaunchKernelGGL(p_update_kernel<decltype(P)>, grid, dim3(kB), 0, c.stream, w);
+        hipLaunchKernelGGL(p_update_kernel<decltype(P)>, grid, dim3(kB), 0, c.stream, w, mode);
         return check_launch("p_update_kernel");
     });
 }
@@ -501,13 +633,15 @@ laph_status blas_xr_update(const Ctx &c, const BlasArgs &a, int prec) {
         return check_launch("xr_update_kernel");
     });
 }
-// grid rows: one per list entry, or a quarter of them in flagged mode (a block
-// then walks several flagged slots; the flagged count is known only on the device)
-static dim3 blas_grid(const BlasArgs &a, int mode) {
-    const int rows = mode == kModeFlagged ? (a.nlist_max + 3) / 4 : a.nlist_max;
-    return dim3(a.nsb, rows > 0 ? rows : 1);
+laph_status blas_xrp_update(const Ctx &c, const BlasArgs &a, int prec) {
+    BlasArgs w = a;
+    w.sb_first = 0;   // every block: sites outside the window may have an x_lo to clear
+    dim3 grid(a.nsb, a.nlist_max);
+    return dispatch_prec(prec, [&](auto P, auto PX) {
+        hipLaunchKernelGGL((xrp_update_kernel<decltype(P), decltype(PX)>), grid, dim3(kB), 0, c.stream, w);
+        return check_launch("xrp_update_kernel");
+    });
 }
-
 laph_status blas_accumulate(const Ctx &c, const BlasArgs &a, int prec, int mode) {
     dim3 grid = blas_grid(a, mode);
     return dispatch_prec(prec, [&](auto, auto PX) {
@@ -532,12 +666,11 @@ laph_status blas_copy64(const Ctx &c, const BlasArgs &a, Operand dst, Operand sr
     hipLaunchKernelGGL(copy64_kernel, grid, dim3(kB), 0, c.stream, a, dst, src, mode);
     return check_launch("copy64_kernel");
 }
-laph_status blas_flag_tiles(const Ctx &c, const FlagArgs &f) {
-    hipLaunchKernelGGL(flag_tiles_kernel, dim3(1), dim3(kB), 0, c.stream, f);
-    return check_launch("flag_tiles_kernel");
-}
 laph_status blas_finalize(const Ctx &c, const FinArgs &f, int what) {
-    hipLaunchKernelGGL(finalize_kernel, dim3(f.nlist_max), dim3(64), 0, c.stream, f, what);
+    // quantities (= waves) of each step
+    const int nq = what == kFinAlpha ? 2 : (what == kFinOmega || what == kFinRho || what == kFinInit) ? 3
+                   : what == kFinOmegaRho ? 8 : what == kFinUpdate ? 4 : 1;
+    hipLaunchKernelGGL(finalize_kernel, dim3(f.nlist_max), dim3(64 * nq), 0, c.stream, f, what);
     return check_launch("finalize_kernel");
 }
 

@@ -29,7 +29,8 @@ struct SlotState {
     int status;       // LAPH_RHS_*
     int flag;         // 1: reliable update requested, 2: update + restart (breakdown)
     int iters, updates, restarts, maxiter;
-    int xlo_zero;     // 1: x_lo is zero (its memory is stale and not read) until the next x/r update
+    int xlo_from;     // iteration whose x/r update is the first to write x_lo: x_lo is zero (its memory
+                      // stale, not read) before it
 };
 
 constexpr int kBlock = 256;     // sites per workgroup of the register form and of the vector kernels
@@ -162,11 +163,12 @@ struct StageSpec {
     int form = kFormRegister;           // kFormRegister: tiles.nr RHS per thread;
                                         // kFormLds: tiles.nr = 4 * RW RHS per workgroup, links in LDS
     const SlotState *slots = nullptr;   // may be null when flagged == 0
-    double *partials = nullptr;         // [slot][3][pstride]
+    double *partials = nullptr;         // [slot][pq][pstride]
     int pstride = 0;                    // partials per quantity per slot (>= stage_nsb)
+    int pq = 3;                         // quantities per slot
     SiteWindow win;                     // output sites computed (the others untouched; a reduction leaves
                                         // the partials of blocks outside it unwritten)
-    SiteWindow win_w;                   // red == 1: w is zero outside this window (not read there) ...
+    SiteWindow win_w;                   // red == 1, 8: w is zero outside this window (not read there) ...
     const int *w_full = nullptr;        // ... unless this device flag is set
 };
 // site blocks of a stage launch (= partial sums it writes per quantity and slot)

@@ -77,6 +77,7 @@ class Solver {
         int *tile64f_slots = nullptr, *tile64f_mass = nullptr;  // FP64 tiles of the flagged slots
         int *list = nullptr, *slot_mass = nullptr, *flist = nullptr;
         int *ntiles = nullptr, *nlist = nullptr, *ntiles64 = nullptr, *ntiles64f = nullptr, *nflist = nullptr;
+        int *fin_done = nullptr;      // workgroups of a finalize that have finished (0 between launches)
         int *rh_full = nullptr;       // set on the device when a restart gives r^ the whole lattice
         int *ints = nullptr;          // integer region the tables are carved from
         size_t nints = 0, nints_used = 0;
@@ -126,6 +127,7 @@ class Solver {
     laph_status clover(int parity, int inverse, Operand in, Operand out, int post, Operand y, double a, double b,
                        int nlist, SiteWindow win = SiteWindow());
     void drop_graph();
+    FlagArgs flag_args() const;
     laph_status iteration(int grow);
     laph_status run_iterations(int k);
     laph_status load_sources(const SourceSpec &src);

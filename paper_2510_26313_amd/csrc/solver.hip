@@ -84,7 +84,7 @@ size_t Solver::layout(const Ctx &c, int ns, int prec, char *base, WS *ws) {
     w.tmp = op(take(ns * hlo), hlo);
     w.x = op(take(ns * hx), hx);
     size_t o_st = take(ns * sizeof(SlotState));
-    size_t o_part = take((size_t)ns * 3 * pstride * sizeof(double));
+    size_t o_part = take((size_t)ns * kSolverPq * pstride * sizeof(double));
     const size_t nints = std::max(table_ints(ns), tune_ints(ns));
     size_t o_ints = take(nints * sizeof(int));
     if (ws && base) {
@@ -116,6 +116,7 @@ void Solver::carve_tables() {
     ws.ntiles64f = ws.flist + ns;
     ws.nflist = ws.ntiles64f + 1;
     ws.rh_full = ws.nflist + 1;
+    ws.fin_done = ws.nflist + 2;
     ws.nints_used = (size_t)(ws.ntiles + 3 - ints);
 }
 
@@ -192,6 +193,7 @@ laph_status Solver::init(Ctx &ctx, int nslots, const laph_solve_params &params, 
     pstride = partial_stride(ctx);
     host_ints.assign(ws.nints_used, 0);
     host_st.assign(ns, SlotState{});
+    LAPH_HIP(hipMemsetAsync(ws.fin_done, 0, sizeof(int), ctx.stream));
     return LAPH_OK;
 }
 
@@ -222,7 +224,6 @@ BlasArgs Solver::blas(int list_max) const {
     a.r64 = ws.E2;
     a.flist = ws.flist;
     a.nflist = ws.nflist;
-    a.win_rh = rh_win;
     a.rh_full = ws.rh_full;
     return a;
 }
@@ -233,6 +234,7 @@ FinArgs Solver::fin(int list_max, int nsb, SiteWindow win, int bs) const {
     f.nlist = ws.nlist;
     f.nlist_max = list_max;
     f.nsb = nsb > 0 ? nsb : nsb256;
+    f.nsb2 = nsb256;
     f.count = window_blocks(win, bs, f.nsb, c->g.vh, &f.first);
     f.pstride = pstride;
     f.st = ws.st;
@@ -341,8 +343,9 @@ laph_status Solver::stage(int sprec, int out_parity, Operand in, Operand out, in
     s.slots = ws.st;
     s.partials = ws.partials;
     s.pstride = pstride;
+    s.pq = kSolverPq;
     s.win = win;
-    s.win_w = rh_win;   // reduction 1: w is r^
+    s.win_w = rh_win;   // reductions 1 and 8: w is r^
     s.w_full = ws.rh_full;
     return launch_stage(*c, s);
 }
@@ -366,22 +369,36 @@ laph_status Solver::clover(int parity, int inverse, Operand in, Operand out, int
     return launch_clover(*c, s);
 }
 
+// where an iteration's last finalize puts the slots flagged for a reliable update (list and FP64 tiles)
+FlagArgs Solver::flag_args() const {
+    FlagArgs fl;
+    fl.tile_slots = ws.tile64_slots;
+    fl.tile_mass = ws.tile64_mass;
+    fl.ntiles = ws.ntiles64;
+    fl.nr = nr64;
+    fl.done = ws.fin_done;
+    fl.out_slots = ws.tile64f_slots;
+    fl.out_mass = ws.tile64f_mass;
+    fl.out_ntiles = ws.ntiles64f;
+    fl.flist = ws.flist;
+    fl.nflist = ws.nflist;
+    return fl;
+}
+
 // ---- one BiCGStab iteration (all kernels device-driven) ---------------------
+// p is ready on entry (the solve's first lower, or the iteration before).
 // grow = j > 0: iteration j of a solve whose b_hat lives on the timeslices t0 +- 1.  Every
 // stage widens the support of its input by one timeslice, so r and p enter iteration j on
-// t0 +- (4 j - 3), v and s live on +- (4 j - 1), t and the new r on +- (4 j + 1): the kernels
-// skip the sites beyond, where every vector is exactly zero (p and tmp are zeroed at the
-// start, the others are not read there).  The skipped sums are sums of zeros, so the
-// iterates do not change by a bit.
+// t0 +- (4 j - 3), v and s live on +- (4 j - 1), t and the new r and p on +- (4 j + 1): the
+// kernels skip the sites beyond, where every vector is exactly zero (tmp is zeroed at the
+// start, p by the first lower, the others are not read there).  The skipped sums are sums of
+// zeros.
 laph_status Solver::iteration(int grow) {
     const Operand none;
     BlasArgs a = blas(ns);
     auto reach = [&](int k) { return grow > 0 ? slab_window(c->g, src_t0, k) : SiteWindow(); };
-    const SiteWindow wp = reach(4 * grow - 3), wv = reach(4 * grow - 1), wt = reach(4 * grow + 1);
+    const SiteWindow wv = reach(4 * grow - 1), wt = reach(4 * grow + 1);
     const int bs = form == kFormLds ? kLdsSites : kBlock;
-    a.win = wp;
-    a.win_pv = grow > 1 ? reach(4 * grow - 5) : SiteWindow();   // (the first p is r)
-    LAPH_TRY(blas_p_update(*c, a, prec));
     // v = M_hat p,  <r^, v>
     LAPH_TRY(stage(prec, 1, ws.p, ws.tmp, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 0, none, 0, reach(4 * grow - 2)));
     LAPH_TRY(stage(prec, 0, ws.tmp, ws.v, 1, 0, none, 0, 1, ws.p, 1.0, none, 0, -0.25, 1, ws.rh, 0, wv));
@@ -389,47 +406,46 @@ laph_status Solver::iteration(int grow) {
     // s = r - alpha v (in r)
     a.win = wv;
     LAPH_TRY(blas_s_update(*c, a, prec));
-    // t = M_hat s,  <t, s>, |t|^2
     LAPH_TRY(stage(prec, 1, ws.r, ws.tmp, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 0, none, 0, reach(4 * grow)));
-    LAPH_TRY(stage(prec, 0, ws.tmp, ws.t, 1, 0, none, 0, 1, ws.r, 1.0, none, 0, -0.25, 2, none, 0, wt));
-    LAPH_TRY(blas_finalize(*c, fin(ns, nsb_inner, wt, bs), kFinOmega));
-    // x_lo += alpha p + omega s;  r = s - omega t;  rho, |r|^2, update decision
+    FinArgs f = fin(ns, nsb_inner, wt, bs);
     a.win = wt;
-    LAPH_TRY(blas_xr_update(*c, a, prec));
-    LAPH_TRY(blas_finalize(*c, fin(ns, 0, wt, kBlock), kFinRho));
-    a.win = SiteWindow();
-    FinArgs f = fin(ns);
-    // compact the slots flagged for a reliable update (list and FP64 tiles)
-    FlagArgs fl;
-    fl.tile_slots = ws.tile64_slots;
-    fl.tile_mass = ws.tile64_mass;
-    fl.ntiles = ws.ntiles64;
-    fl.nr = nr64;
-    fl.st = ws.st;
-    fl.out_slots = ws.tile64f_slots;
-    fl.out_mass = ws.tile64f_mass;
-    fl.out_ntiles = ws.ntiles64f;
-    fl.flist = ws.flist;
-    fl.nflist = ws.nflist;
-    LAPH_TRY(blas_flag_tiles(*c, fl));
+    a.win_pv = wv;
+    const bool confined = rh_win.n > 0;   // r^ on the source's window
+    if (confined) {
+        // t = M_hat s,  <t, s>, |t|^2, |s|^2, <r^, t>: omega, rho, beta, |r|^2, the update decision;
+        // x_lo += alpha p + omega s;  r = s - omega t;  p = r + beta (p - omega v) unless flagged
+        LAPH_TRY(stage(prec, 0, ws.tmp, ws.t, 1, 0, none, 0, 1, ws.r, 1.0, none, 0, -0.25, 8, ws.rh, 0, wt));
+        f.flags = flag_args();
+        LAPH_TRY(blas_finalize(*c, f, kFinOmegaRho));
+        LAPH_TRY(blas_xrp_update(*c, a, prec));
+    } else {
+        // t = M_hat s,  <t, s>, |t|^2;  x_lo += alpha p + omega s;  r = s - omega t;  rho, |r|^2, update
+        // decision
+        LAPH_TRY(stage(prec, 0, ws.tmp, ws.t, 1, 0, none, 0, 1, ws.r, 1.0, none, 0, -0.25, 2, none, 0));
+        LAPH_TRY(blas_finalize(*c, f, kFinOmega));
+        LAPH_TRY(blas_xr_update(*c, a, prec));
+        f = fin(ns);
+        f.flags = flag_args();
+        LAPH_TRY(blas_finalize(*c, f, kFinRho));
+    }
+    BlasArgs u = blas(ns);
     // reliable update of the flagged slots: x64 += x_lo and the FP64 residual of x64.
     // With an FP32 x_lo and the LDS form the residual follows the same exact correction,
     // r64 -= M_hat x_lo in FP64 arithmetic on the widened x_lo (the stages read x_lo, half
     // the bytes of x64, and r64 in place of b_hat), and the second stage also folds x_lo
-    // into x64 (x_lo of a flagged slot is never marked zero here: every iteration's x/r
-    // update writes it before the update decision); otherwise x64 += x_lo, then
+    // into x64 (x_lo of a flagged slot was just written by the x/r update); otherwise x64 += x_lo, then
     // r64 = b_hat - M_hat x64
     if (prec != LAPH_F64 && form64 == kFormLds) {
         LAPH_TRY(stage(LAPH_F64, 1, ws.x, ws.O0, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 6, none, 1));
         LAPH_TRY(stage(LAPH_F64, 0, ws.O0, ws.E2, 1, 0, none, 0, 2, ws.E2, 1.0, ws.x, -1.0, 0.25, 7, ws.E1, 1));
     } else {
-        LAPH_TRY(blas_accumulate(*c, a, prec, kModeFlagged));
+        LAPH_TRY(blas_accumulate(*c, u, prec, kModeFlagged));
         LAPH_TRY(stage(LAPH_F64, 1, ws.E1, ws.O0, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 0, none, 1));
         LAPH_TRY(stage(LAPH_F64, 0, ws.O0, ws.E2, 1, 0, none, 0, 2, ws.E0, 1.0, ws.E1, -1.0, 0.25, 3, none, 1));
     }
+    LAPH_TRY(blas_lower(*c, u, prec, kModeFlagged, 0));
     LAPH_TRY(blas_finalize(*c, fin(ns, nsb64), kFinUpdate));
-    LAPH_TRY(blas_lower(*c, a, prec, kModeFlagged, 0));
-    LAPH_TRY(blas_finalize(*c, f, kFinRho2));
+    LAPH_TRY(blas_p_update(*c, a, prec, confined ? kModeUpdated : kModeActive));
     return LAPH_OK;
 }
 
@@ -574,12 +590,8 @@ laph_status Solver::solve(const SourceSpec &src, const std::vector<int> &slot_ma
         // than 0.5 ms, about 20 launches of 5 us, and the graph's replay is as fast
         int grow = 0;
         if (slab && pass == 0 && (size_t)c->g.vh * ncur >= ((size_t)1 << 20))
-            while (2 * (4 * (grow + 1) - 5) + 1 < c->g.lt) ++grow;
-        if (grow == 1) grow = 0;   // (a lattice of few timeslices)
-        if (grow > 0) {
-            LAPH_HIP(hipMemsetAsync(ws.p.base, 0, ws.p.stride * n, c->stream));
-            LAPH_HIP(hipMemsetAsync(ws.tmp.base, 0, ws.tmp.stride * n, c->stream));
-        }
+            while (2 * (4 * (grow + 1) - 2) + 1 < c->g.lt) ++grow;
+        if (grow > 0) LAPH_HIP(hipMemsetAsync(ws.tmp.base, 0, ws.tmp.stride * n, c->stream));
         int guard = 0;
         while (!active.empty()) {
             if (guard * K < grow) {
