@@ -614,178 +614,280 @@ __global__ __launch_bounds__(kMB) void mg_prolong32_kernel(Geom g, MgDev m, cons
 // ---------------------------------------------------------------------------
 // coarse operator and coarse BiCGStab (FP64, coarse vectors [n][nc][ncv])
 // ---------------------------------------------------------------------------
-// out_r = D_c in_r.  Grid (nc, RHS groups), kMB threads: for each of the 9 directions the
-// block row C[a][d] and the neighbour's coarse vectors of the group's RHS are staged in
-// LDS (coalesced), then each thread accumulates up to kCoarsePairs (row, RHS) outputs, so
-// every block row is read from memory once per group.
-constexpr int kCoarsePairs = 4;
-inline int coarse_group(int ncv) { return std::min(64, kCoarsePairs * kMB / ncv); }
-
-__global__ __launch_bounds__(kMB) void mg_coarse_apply_kernel(MgDev m, const double2 *C, const double2 *in,
-                                                              double2 *out, int n, int group) {
-    extern __shared__ double2 lds[];
-    double2 *ct = lds;                                    // ncv x ncv block
-    double2 *xt = lds + (size_t)m.ncv * m.ncv;            // group x ncv neighbour vectors
-    const int a = blockIdx.x, r0 = blockIdx.y * group;
-    const int g = min(group, n - r0);
-    const int npair = m.ncv * g, nblk = m.ncv * m.ncv;
-    double acc[2 * kCoarsePairs];
-#pragma unroll
-    for (int k = 0; k < 2 * kCoarsePairs; ++k) acc[k] = 0.0;
-    for (int d = 0; d < 9; ++d) {
-        const int nb = coarse_nbr(m, a, d);
-        __syncthreads();
-        const double2 *cb = C + ((size_t)a * 9 + d) * nblk;
-        for (int i = threadIdx.x; i < nblk; i += kMB) ct[i] = cb[i];
-        for (int i = threadIdx.x; i < npair; i += kMB) {
-            const int rl = i / m.ncv, col = i - rl * m.ncv;
-            xt[i] = in[((size_t)(r0 + rl) * m.nc + nb) * m.ncv + col];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kCoarsePairs; ++k) {
-            const int pidx = threadIdx.x + k * kMB;
-            if (pidx < npair) {
-                const int rl = pidx / m.ncv, row = pidx - rl * m.ncv;
-                const double2 *crow = ct + (size_t)row * m.ncv, *x = xt + (size_t)rl * m.ncv;
-                double sr = acc[2 * k], si = acc[2 * k + 1];
-                for (int col = 0; col < m.ncv; ++col) {
-                    const double2 cc = crow[col], vv = x[col];
-                    sr += cc.x * vv.x - cc.y * vv.y;
-                    si += cc.x * vv.y + cc.y * vv.x;
-                }
-                acc[2 * k] = sr;
-                acc[2 * k + 1] = si;
-            }
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < kCoarsePairs; ++k) {
-        const int pidx = threadIdx.x + k * kMB;
-        if (pidx < npair) {
-            const int rl = pidx / m.ncv, row = pidx - rl * m.ncv;
-            out[((size_t)(r0 + rl) * m.nc + a) * m.ncv + row] = make_double2(acc[2 * k], acc[2 * k + 1]);
-        }
-    }
-}
-
+// Scalars of one RHS.  A kernel of the coarse solve has every workgroup read them and its RHS's
+// workgroup 0 write those that no workgroup of that kernel reads (rho alternates); done is
+// written where every workgroup draws the same conclusion from the same sums.
 struct CgState {
-    double2 rho, alpha, omega, beta;
-    double b2, r2, tol2;
+    double2 rho[2], alpha, omega;
+    double tol2;
     int done;
 };
 
-// partial[(r * 2 + q) * 2 + (re, im)][blk] of <x_q, y_q> over len complex entries
-__global__ __launch_bounds__(kMB) void mg_cdot_kernel(const double2 *x0, const double2 *y0, const double2 *x1,
-                                                      const double2 *y1, int nq, size_t len, double *partial) {
-    __shared__ double red[(kMB / 64) * 4];
-    const int r = blockIdx.y;
-    double v[4] = {0, 0, 0, 0};
-    for (size_t i = (size_t)blockIdx.x * kMB + threadIdx.x; i < len; i += (size_t)gridDim.x * kMB) {
-        const size_t o = (size_t)r * len + i;
-        const double2 a = x0[o], b = y0[o];
-        v[0] += a.x * b.x + a.y * b.y;
-        v[1] += a.x * b.y - a.y * b.x;
-        if (nq > 1) {
-            const double2 c = x1[o], d = y1[o];
-            v[2] += c.x * d.x + c.y * d.y;
-            v[3] += c.x * d.y - c.y * d.x;
-        }
-    }
-    block_sum_bcast<4>(v, red);
-    if (threadIdx.x < 4) partial[((size_t)r * 4 + threadIdx.x) * gridDim.x + blockIdx.x] = v[threadIdx.x];
+__device__ __forceinline__ int cg_done(const CgState &s) {
+    return __hip_atomic_load(&s.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
-enum { kCgInit, kCgRho, kCgAlpha, kCgOmega, kCgRes };
-
-// Sum the partials of RHS blockIdx.x (fixed order) and advance its BiCGStab scalars.
-__global__ __launch_bounds__(kMB) void mg_cscalar_kernel(CgState *st, const double *partial, int nblk, int what,
-                                                         double tol) {
-    __shared__ double red[(kMB / 64) * 4];
-    const int r = blockIdx.x;
-    double v[4] = {0, 0, 0, 0};
-    for (int b = threadIdx.x; b < nblk; b += kMB)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] += partial[((size_t)r * 4 + q) * nblk + b];
-    block_sum_bcast<4>(v, red);
-    if (threadIdx.x != 0) return;
-    CgState &s = st[r];
-    auto cdiv = [](double2 a, double2 b) {
-        const double d = b.x * b.x + b.y * b.y;
-        return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
-    };
-    auto cmul = [](double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); };
-    if (what == kCgInit) {   // v0 = <b, b>
-        s.b2 = v[0];
-        s.r2 = v[0];
-        s.tol2 = tol * tol * v[0];
-        s.rho = s.alpha = s.omega = make_double2(1.0, 0.0);
-        s.beta = make_double2(0.0, 0.0);
-        s.done = !(v[0] > 0);
-        return;
-    }
-    if (s.done) return;
-    if (what == kCgRho) {   // v0,1 = <r^, r>
-        const double2 rn = make_double2(v[0], v[1]);
-        if (rn.x == 0 && rn.y == 0) {
-            s.done = 1;
-            return;
-        }
-        s.beta = cmul(cdiv(rn, s.rho), cdiv(s.alpha, s.omega));
-        s.rho = rn;
-    } else if (what == kCgAlpha) {   // v0,1 = <r^, v>
-        const double2 sg = make_double2(v[0], v[1]);
-        if (sg.x == 0 && sg.y == 0) {
-            s.done = 1;
-            return;
-        }
-        s.alpha = cdiv(s.rho, sg);
-    } else if (what == kCgOmega) {   // v0,1 = <t, s>, v2 = <t, t>
-        // t = 0 means s = 0: omega = 0 still takes x += alpha p and r = s
-        s.omega = v[2] > 0 ? make_double2(v[0] / v[2], v[1] / v[2]) : make_double2(0.0, 0.0);
-    } else if (what == kCgRes) {   // v0 = <r, r>
-        s.r2 = v[0];
-        if (v[0] <= s.tol2) s.done = 1;
-    }
+__device__ __forceinline__ void cg_set_done(CgState &s, int done) {
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(&s.done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
 __device__ __forceinline__ double2 cm(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
+__device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
+    const double d = b.x * b.x + b.y * b.y;
+    return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
+}
+// add <a, b> to v0,1
+__device__ __forceinline__ void cg_mac(double *v, double2 a, double2 b) {
+    v[0] += a.x * b.x + a.y * b.y;
+    v[1] += a.x * b.y - a.y * b.x;
+}
 
-// kind 0: p = r + beta (p - omega v); 1: s = r - alpha v; 2: x += alpha p + omega s, r = s - omega t;
-// 3: x = 0, r = r^ = b, p = v = 0
-__global__ __launch_bounds__(kMB) void mg_cupdate_kernel(const CgState *st, int kind, size_t len, double2 *x,
-                                                         double2 *r, double2 *rh, double2 *p, double2 *v, double2 *s,
-                                                         double2 *t, const double2 *b) {
-    const int rr = blockIdx.y;
-    const CgState &S = st[rr];
-    if (kind != 3 && S.done) return;
-    for (size_t i = (size_t)blockIdx.x * kMB + threadIdx.x; i < len; i += (size_t)gridDim.x * kMB) {
-        const size_t o = (size_t)rr * len + i;
-        if (kind == 0) {
-            const double2 pv = p[o], vv = v[o], rv = r[o];
-            const double2 w = cm(S.omega, vv);
-            const double2 q = cm(S.beta, make_double2(pv.x - w.x, pv.y - w.y));
-            p[o] = make_double2(rv.x + q.x, rv.y + q.y);
-        } else if (kind == 1) {
-            const double2 vv = v[o], rv = r[o];
-            const double2 w = cm(S.alpha, vv);
-            s[o] = make_double2(rv.x - w.x, rv.y - w.y);
-        } else if (kind == 2) {
-            const double2 ap = cm(S.alpha, p[o]), os = cm(S.omega, s[o]), ot = cm(S.omega, t[o]);
-            const double2 xv = x[o], sv = s[o];
-            x[o] = make_double2(xv.x + ap.x + os.x, xv.y + ap.y + os.y);
-            r[o] = make_double2(sv.x - ot.x, sv.y - ot.y);
-        } else {
-            const double2 bv = b[o];
-            x[o] = make_double2(0.0, 0.0);
-            r[o] = bv;
-            rh[o] = bv;
-            p[o] = make_double2(0.0, 0.0);
-            v[o] = make_double2(0.0, 0.0);
+// out_r = D_c in_r.  A workgroup of kMB threads takes one site and up to 4 groups of R RHS: 8 lanes
+// own a block row, so a group takes a wave for every 8 of the ncv <= 32 rows.  Grid: 8 ceil(nc / 8)
+// sites times the workgroups that the RHS need (coarse_wgs), those of a site 8 apart, which is on
+// one XCD, so that all but one of them find the block row in its L2.  The 9 neighbours' vectors are
+// staged in LDS at once; a lane reads the row's elements from memory straight into registers, every
+// 8th column, those of the next step ahead of the products, and keeps the sums of R RHS; of these
+// it ends with one.
+// DOT 1: partial sums <u, out>; 2: <out, u>, <out, out>, [n][3][nc], one per site (u: a coarse
+// vector), so the solve needs no sweep for them.
+// Bound by latency at small nc: with the blocks staged in LDS per direction (9 serial rounds of
+// load, barrier and LDS reads in the products' chain) coarse 4^3 x 8, 24 components, 8 RHS took
+// 31 us, double-buffered 29 us, now 20 us; its 42 MB take 7 us at the copy rate.  Coarse 8^4: 179 us,
+// now 108 us (8 RHS); 672 us, now 346 us (40); a lone RHS, which has its own R, 121 us, now 78 us.
+constexpr int kCoarseRhs = 8;
+__host__ __device__ inline int coarse_waves(int ncv) { return ncv > 16 ? 4 : (ncv > 8 ? 2 : 1); }   // of a group
+template <int R>
+__host__ __device__ inline int coarse_wgs(int ncv, int n) {
+    const int per = R * (kMB / 64 / coarse_waves(ncv));
+    return (n + per - 1) / per;
+}
+
+template <int DOT, int R>
+__global__ __launch_bounds__(kMB) void mg_coarse_apply_kernel(MgDev m, const double2 *C, const double2 *in,
+                                                              double2 *out, int n, const CgState *st,
+                                                              const double2 *u, double *partial) {
+    extern __shared__ double2 xt[];   // [9][per][ncv]
+    __shared__ int nbr[9];
+    __shared__ double red[(kMB / 64) * 3 * 8];
+    const int ncv = m.ncv, ng = coarse_wgs<R>(ncv, n), a = blockIdx.x / (8 * ng) * 8 + (blockIdx.x & 7);
+    if (a >= m.nc) return;
+    const int wave = threadIdx.x >> 6, nw = coarse_waves(ncv), per = R * (kMB / 64 / nw), sub = wave / nw;
+    const int first = blockIdx.x / 8 % ng * per, all = min(per, n - first);   // this workgroup's RHS
+    const int r0 = first + sub * R, g = min(R, n - r0);                       // this wave's
+    const int row = (wave - sub * nw) * 8 + (threadIdx.x >> 3 & 7), cg = threadIdx.x & 7;
+    // nothing reads the product of an RHS that is done (each wave looks at all of the workgroup's)
+    if constexpr (DOT != 0)
+        if (!__any(!st[first + min((int)(threadIdx.x & 63), all - 1)].done)) return;
+    const bool live = row < ncv;
+    const double2 *crow = C + (size_t)a * 9 * ncv * ncv + (live ? row : 0) * ncv;
+    double2 cc[9], cn[9];
+    auto load = [&](int col) {
+#pragma unroll
+        for (int d = 0; d < 9; ++d) cn[d] = crow[d * ncv * ncv + min(col, ncv - 1)];
+    };
+    load(cg);
+    if (threadIdx.x < 9) nbr[threadIdx.x] = coarse_nbr(m, a, threadIdx.x);
+    __syncthreads();
+    constexpr int kEach = (9 * R * 2 * kMgMaxVec + kMB - 1) / kMB;   // all in flight at once
+    double2 xs[kEach];
+    const int nx = 9 * per * ncv;
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+        const int i = min((int)threadIdx.x + j * kMB, nx - 1), k = i / ncv, col = i - k * ncv;
+        const int d = k / per, rl = min(k - d * per, all - 1);
+        xs[j] = in[((size_t)(first + rl) * m.nc + nbr[d]) * ncv + col];
+    }
+#pragma unroll
+    for (int j = 0; j < kEach; ++j)
+        if (threadIdx.x + j * kMB < nx) xt[threadIdx.x + j * kMB] = xs[j];
+    __syncthreads();
+    double v[2 * R];
+#pragma unroll
+    for (int k = 0; k < 2 * R; ++k) v[k] = 0.0;
+    for (int col = cg; col < ncv + cg; col += 8) {
+#pragma unroll
+        for (int d = 0; d < 9; ++d) cc[d] = col < ncv ? cn[d] : make_double2(0.0, 0.0);
+        load(col + 8);
+        const double2 *x = xt + sub * R * ncv + min(col, ncv - 1);
+#pragma unroll
+        for (int d = 0; d < 9; ++d)
+#pragma unroll
+            for (int rl = 0; rl < R; ++rl) {
+                const double2 w = x[(d * per + rl) * ncv];
+                v[2 * rl] = fma(cc[d].x, w.x, fma(-cc[d].y, w.y, v[2 * rl]));
+                v[2 * rl + 1] = fma(cc[d].x, w.y, fma(cc[d].y, w.x, v[2 * rl + 1]));
+            }
+    }
+    // sum over the 8 lanes of a row, halving the RHS that a lane holds where there are several:
+    // lane cg < R is left with RHS cg
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) {
+        const bool hi = cg & off;
+#pragma unroll
+        for (int k = 0; k < 2 * (off < R ? off : R); ++k) {
+            const double other = off < R ? v[k + 2 * off] : v[k];
+            v[k] = (hi ? other : v[k]) + __shfl_xor(hi ? v[k] : other, off, 64);
         }
     }
+    const double2 y = make_double2(v[0], v[1]);
+    const size_t o = ((size_t)(r0 + cg) * m.nc + a) * ncv + row;
+    const bool own = live && cg < g;
+    if (own) out[o] = y;
+    if constexpr (DOT != 0) {
+        double d[3] = {0.0, 0.0, 0.0};
+        if (own) {
+            const double2 w = u[o];
+            if (DOT == 1) cg_mac(d, w, y);
+            if (DOT == 2) cg_mac(d, y, w), d[2] = y.x * y.x + y.y * y.y;
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int off = 32; off > 4; off >>= 1) d[q] += __shfl_xor(d[q], off, 64);
+        if ((threadIdx.x & 63) < 8)
+            for (int q = 0; q < 3; ++q) red[(wave * 3 + q) * 8 + cg] = d[q];
+        __syncthreads();
+        const int q = threadIdx.x >> 3 & 7;
+        if (wave == sub * nw && q < 3 && cg < g) {
+            double t = 0.0;
+            for (int w = wave; w < wave + nw; ++w) t += red[(w * 3 + q) * 8 + cg];
+            partial[((size_t)(r0 + cg) * 3 + q) * m.nc + a] = t;
+        }
+    }
+}
+
+// v = the sums of partial[r][3][np] in a fixed order, in every thread
+__device__ __forceinline__ void cg_sum(double (&v)[3], const double *partial, int r, int np, double *red) {
+    for (int q = 0; q < 3; ++q) v[q] = 0.0;
+    for (int b = threadIdx.x; b < np; b += kMB)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) v[q] += partial[((size_t)r * 3 + q) * np + b];
+    block_sum_bcast<3>(v, red);
+}
+
+// partial[r][3][np] -> out[r][3][kCoarseChunks].  The consumers below each add all partials of
+// their RHS themselves, which takes the place of a launch per sum as long as these are few.
+constexpr int kCoarseChunks = 16, kCoarseFew = 1024;
+__global__ __launch_bounds__(kMB) void mg_csum_kernel(const double *partial, int np, double *out) {
+    __shared__ double red[(kMB / 64) * 3];
+    const int r = blockIdx.y, per = (np + kCoarseChunks - 1) / kCoarseChunks, b0 = blockIdx.x * per;
+    double v[3] = {0.0, 0.0, 0.0};
+    for (int b = b0 + threadIdx.x; b < min(np, b0 + per); b += kMB)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) v[q] += partial[((size_t)r * 3 + q) * np + b];
+    block_sum_bcast<3>(v, red);
+    if (threadIdx.x < 3) out[((size_t)r * 3 + threadIdx.x) * kCoarseChunks + blockIdx.x] = v[threadIdx.x];
+}
+
+// The vectors of the coarse BiCGStab: len entries for each RHS.
+struct CgVec {
+    double2 *x, *r, *rh, *p, *v, *s, *t;
+    const double2 *b;
+};
+
+// x = 0, r = r^ = b, p = v = 0, with partial sums <r^, r>, <r, r>.  Grid (blocks, n), as the
+// three kernels after it.
+__global__ __launch_bounds__(kMB) void mg_cinit_kernel(CgState *st, size_t len, CgVec f, double *partial) {
+    __shared__ double red[(kMB / 64) * 3];
+    const int rr = blockIdx.y;
+    double v[3] = {0.0, 0.0, 0.0};
+    for (size_t i = (size_t)blockIdx.x * kMB + threadIdx.x; i < len; i += (size_t)gridDim.x * kMB) {
+        const size_t o = (size_t)rr * len + i;
+        const double2 b = f.b[o];
+        f.x[o] = f.p[o] = f.v[o] = make_double2(0.0, 0.0);
+        f.r[o] = f.rh[o] = b;
+        cg_mac(v, b, b);
+        v[2] += b.x * b.x + b.y * b.y;
+    }
+    block_sum_bcast<3>(v, red);
+    if (threadIdx.x < 3) partial[((size_t)rr * 3 + threadIdx.x) * gridDim.x + blockIdx.x] = v[threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        CgState &s = st[rr];
+        s.rho[1] = s.alpha = s.omega = make_double2(1.0, 0.0);
+        s.done = 0;
+    }
+}
+
+// p = r + beta (p - omega v), from the sums <r^, r>, <r, r> of the r before; ends the RHS whose
+// |r| is below tol |b|.
+__global__ __launch_bounds__(kMB) void mg_cp_kernel(CgState *st, int it, size_t len, CgVec f, const double *partial,
+                                                    int np, double tol) {
+    __shared__ double red[(kMB / 64) * 3];
+    const int rr = blockIdx.y;
+    CgState &s = st[rr];
+    if (it > 0 && cg_done(s)) return;
+    double v[3];
+    cg_sum(v, partial, rr, np, red);
+    const double2 rho = make_double2(v[0], v[1]);
+    if ((it == 0 ? !(v[2] > 0) : v[2] <= s.tol2) || (rho.x == 0 && rho.y == 0)) {
+        cg_set_done(s, 1);
+        return;
+    }
+    const double2 omega = s.omega, beta = cm(cdiv(rho, s.rho[(it + 1) & 1]), cdiv(s.alpha, omega));
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        s.rho[it & 1] = rho;
+        if (it == 0) s.tol2 = tol * tol * v[2];
+    }
+    for (size_t i = (size_t)blockIdx.x * kMB + threadIdx.x; i < len; i += (size_t)gridDim.x * kMB) {
+        const size_t o = (size_t)rr * len + i;
+        const double2 pv = f.p[o], rv = f.r[o], w = cm(omega, f.v[o]);
+        const double2 q = cm(beta, make_double2(pv.x - w.x, pv.y - w.y));
+        f.p[o] = make_double2(rv.x + q.x, rv.y + q.y);
+    }
+}
+
+// s = r - alpha v, from the sum <r^, v>
+__global__ __launch_bounds__(kMB) void mg_cs_kernel(CgState *st, int it, size_t len, CgVec f, const double *partial,
+                                                    int np) {
+    __shared__ double red[(kMB / 64) * 3];
+    const int rr = blockIdx.y;
+    CgState &s = st[rr];
+    if (cg_done(s)) return;
+    double v[3];
+    cg_sum(v, partial, rr, np, red);
+    if (v[0] == 0 && v[1] == 0) {
+        cg_set_done(s, 1);
+        return;
+    }
+    const double2 alpha = cdiv(s.rho[it & 1], make_double2(v[0], v[1]));
+    if (blockIdx.x == 0 && threadIdx.x == 0) s.alpha = alpha;
+    for (size_t i = (size_t)blockIdx.x * kMB + threadIdx.x; i < len; i += (size_t)gridDim.x * kMB) {
+        const size_t o = (size_t)rr * len + i;
+        const double2 rv = f.r[o], w = cm(alpha, f.v[o]);
+        f.s[o] = make_double2(rv.x - w.x, rv.y - w.y);
+    }
+}
+
+// x += alpha p + omega s, r = s - omega t, from the sums <t, s>, <t, t>, with the partial sums
+// <r^, r>, <r, r> of the new r.
+__global__ __launch_bounds__(kMB) void mg_cxr_kernel(CgState *st, size_t len, CgVec f, const double *partial, int np,
+                                                     double *next) {
+    __shared__ double red[(kMB / 64) * 3];
+    const int rr = blockIdx.y;
+    CgState &s = st[rr];
+    if (cg_done(s)) return;
+    double v[3];
+    cg_sum(v, partial, rr, np, red);
+    // t = 0 means s = 0: omega = 0 still takes x += alpha p and r = s
+    const double2 alpha = s.alpha;
+    const double2 omega = v[2] > 0 ? make_double2(v[0] / v[2], v[1] / v[2]) : make_double2(0.0, 0.0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) s.omega = omega;
+    double sum[3] = {0.0, 0.0, 0.0};
+    for (size_t i = (size_t)blockIdx.x * kMB + threadIdx.x; i < len; i += (size_t)gridDim.x * kMB) {
+        const size_t o = (size_t)rr * len + i;
+        const double2 sv = f.s[o], xv = f.x[o];
+        const double2 ap = cm(alpha, f.p[o]), os = cm(omega, sv), ot = cm(omega, f.t[o]);
+        const double2 rv = make_double2(sv.x - ot.x, sv.y - ot.y);
+        f.x[o] = make_double2(xv.x + ap.x + os.x, xv.y + ap.y + os.y);
+        f.r[o] = rv;
+        cg_mac(sum, f.rh[o], rv);
+        sum[2] += rv.x * rv.x + rv.y * rv.y;
+    }
+    __syncthreads();   // red is free again
+    block_sum_bcast<3>(sum, red);
+    if (threadIdx.x < 3) next[((size_t)rr * 3 + threadIdx.x) * gridDim.x + blockIdx.x] = sum[threadIdx.x];
 }
 
 // ---------------------------------------------------------------------------
@@ -1236,18 +1338,29 @@ laph_status mg_prolong_canonical(const Ctx &c, double *f, const double *cvec, in
     return unpack_spinor(c, f, fo, LAPH_F64, n, -1, 0);
 }
 
-static laph_status coarse_apply_dev(const Ctx &c, double2 *out, const double2 *in, int n) {
+// DOT, st, u, partial: as of the kernel
+template <int DOT, int R>
+static laph_status coarse_apply_rhs(const Ctx &c, double2 *out, const double2 *in, int n, const CgState *st,
+                                    const double2 *u, double *partial) {
     const MgState &s = c.mgs;
-    const int group = coarse_group(s.geo.ncv);
-    const size_t lds = ((size_t)s.geo.ncv * s.geo.ncv + (size_t)group * s.geo.ncv) * sizeof(double2);
-    hipLaunchKernelGGL(mg_coarse_apply_kernel, dim3(s.geo.nc, (n + group - 1) / group), dim3(kMB), lds, c.stream,
-                       mg_dev(s.geo), (const double2 *)s.coarse, in, out, n, group);
+    const int per = R * (kMB / 64 / coarse_waves(s.geo.ncv));
+    const size_t lds = (size_t)9 * per * s.geo.ncv * sizeof(double2);   // 36 KB at most
+    hipLaunchKernelGGL((mg_coarse_apply_kernel<DOT, R>), dim3((s.geo.nc + 7) / 8 * 8 * coarse_wgs<R>(s.geo.ncv, n)),
+                       dim3(kMB), lds, c.stream, mg_dev(s.geo), (const double2 *)s.coarse, in, out, n, st, u, partial);
     return check_launch("mg_coarse_apply_kernel");
+}
+
+template <int DOT>
+static laph_status coarse_apply_dev(const Ctx &c, double2 *out, const double2 *in, int n, const CgState *st,
+                                    const double2 *u, double *partial) {
+    return n == 1 ? coarse_apply_rhs<DOT, 1>(c, out, in, n, st, u, partial)
+                  : coarse_apply_rhs<DOT, kCoarseRhs>(c, out, in, n, st, u, partial);
 }
 
 laph_status mg_coarse_apply(const Ctx &c, double *out, const double *in, int n) {
     LAPH_TRY(need_mg(c));
-    return coarse_apply_dev(c, reinterpret_cast<double2 *>(out), reinterpret_cast<const double2 *>(in), n);
+    return coarse_apply_dev<0>(c, reinterpret_cast<double2 *>(out), reinterpret_cast<const double2 *>(in), n, nullptr,
+                               nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1263,6 +1376,8 @@ struct MgWs {
     // coarse vectors [n][nc][ncv]
     double2 *cb, *cx, *cr, *crh, *cp, *cv, *cs, *ct;
     CgState *cst;
+    double *cpart;    // coarse partials [n][3][nc]
+    double *csums;    // [n][3][kCoarseChunks]
     GcrState *gst;
     double *spart;    // stage partials [n][3][pstride]
     double *dots;     // [n][3]
@@ -1298,6 +1413,8 @@ size_t mg_layout(const Ctx &c, int n, int restart, char *base, MgWs *w) {
     double2 **cv[8] = {&t.cb, &t.cx, &t.cr, &t.crh, &t.cp, &t.cv, &t.cs, &t.ct};
     for (auto p : cv) *p = reinterpret_cast<double2 *>(take(n * cvec));
     t.cst = reinterpret_cast<CgState *>(take(n * sizeof(CgState)));
+    t.cpart = reinterpret_cast<double *>(take((size_t)n * 3 * g.nc * sizeof(double)));
+    t.csums = reinterpret_cast<double *>(take((size_t)n * 3 * kCoarseChunks * sizeof(double)));
     t.gst = reinterpret_cast<GcrState *>(take(n * sizeof(GcrState)));
     t.spart = reinterpret_cast<double *>(take((size_t)n * 3 * partial_stride(c) * sizeof(double)));
     t.dots = reinterpret_cast<double *>(take((size_t)n * 3 * sizeof(double)));
@@ -1438,33 +1555,39 @@ laph_status MgSolver::apply_d32(Operand in, Operand out) {
     return LAPH_OK;
 }
 
+// Five launches an iteration (seven with more than kCoarseFew coarse sites): the kernel that makes
+// a vector leaves its partial sums, the next one adds them and computes the scalars in every
+// workgroup.  With a launch for each sum and one for each set of scalars it took 13 launches and
+// 107 us of kernels (coarse 4^3 x 8, 24 components, 8 RHS), now about 50 us; a sum finished by its last
+// workgroup (7 launches) took 98 us, the release and acquire costing what the launch had.
+// An RHS that is done leaves the rest at once, its products too when all of its group are.
 laph_status MgSolver::coarse_solve() {
     const size_t len = (size_t)s.geo.nc * s.geo.ncv;
     const dim3 g(cblk, n);
-    auto upd = [&](int kind) {
-        hipLaunchKernelGGL(mg_cupdate_kernel, g, dim3(kMB), 0, c.stream, (const CgState *)w.cst, kind, len, w.cx, w.cr,
-                           w.crh, w.cp, w.cv, w.cs, w.ct, (const double2 *)w.cb);
-        return check_launch("mg_cupdate_kernel");
+    const CgVec f{w.cx, w.cr, w.crh, w.cp, w.cv, w.cs, w.ct, w.cb};
+    const bool few = s.geo.nc <= kCoarseFew;
+    const double *sums = few ? w.cpart : w.csums;
+    const int np = few ? s.geo.nc : kCoarseChunks;
+    auto add = [&]() {
+        if (few) return LAPH_OK;
+        hipLaunchKernelGGL(mg_csum_kernel, dim3(kCoarseChunks, n), dim3(kMB), 0, c.stream, (const double *)w.cpart,
+                           s.geo.nc, w.csums);
+        return check_launch("mg_csum_kernel");
     };
-    auto dot = [&](const double2 *a0, const double2 *b0, const double2 *a1, const double2 *b1, int nq, int what) {
-        hipLaunchKernelGGL(mg_cdot_kernel, g, dim3(kMB), 0, c.stream, a0, b0, a1, b1, nq, len, w.bpart);
-        LAPH_TRY(check_launch("mg_cdot_kernel"));
-        hipLaunchKernelGGL(mg_cscalar_kernel, dim3(n), dim3(kMB), 0, c.stream, w.cst, (const double *)w.bpart, cblk,
-                           what, s.coarse_tol);
-        return check_launch("mg_cscalar_kernel");
-    };
-    LAPH_TRY(upd(3));
-    LAPH_TRY(dot(w.cb, w.cb, nullptr, nullptr, 1, kCgInit));
+    hipLaunchKernelGGL(mg_cinit_kernel, g, dim3(kMB), 0, c.stream, w.cst, len, f, w.bpart);
+    LAPH_TRY(check_launch("mg_cinit_kernel"));
     for (int it = 0; it < s.coarse_iters; ++it) {
-        LAPH_TRY(dot(w.crh, w.cr, nullptr, nullptr, 1, kCgRho));
-        LAPH_TRY(upd(0));
-        LAPH_TRY(coarse_apply_dev(c, w.cv, w.cp, n));
-        LAPH_TRY(dot(w.crh, w.cv, nullptr, nullptr, 1, kCgAlpha));
-        LAPH_TRY(upd(1));
-        LAPH_TRY(coarse_apply_dev(c, w.ct, w.cs, n));
-        LAPH_TRY(dot(w.ct, w.cs, w.ct, w.ct, 2, kCgOmega));
-        LAPH_TRY(upd(2));
-        LAPH_TRY(dot(w.cr, w.cr, nullptr, nullptr, 1, kCgRes));
+        hipLaunchKernelGGL(mg_cp_kernel, g, dim3(kMB), 0, c.stream, w.cst, it, len, f, (const double *)w.bpart, cblk,
+                           s.coarse_tol);
+        LAPH_TRY(check_launch("mg_cp_kernel"));
+        LAPH_TRY(coarse_apply_dev<1>(c, w.cv, w.cp, n, w.cst, w.crh, w.cpart));
+        LAPH_TRY(add());
+        hipLaunchKernelGGL(mg_cs_kernel, g, dim3(kMB), 0, c.stream, w.cst, it, len, f, sums, np);
+        LAPH_TRY(check_launch("mg_cs_kernel"));
+        LAPH_TRY(coarse_apply_dev<2>(c, w.ct, w.cs, n, w.cst, w.cs, w.cpart));
+        LAPH_TRY(add());
+        hipLaunchKernelGGL(mg_cxr_kernel, g, dim3(kMB), 0, c.stream, w.cst, len, f, sums, np, w.bpart);
+        LAPH_TRY(check_launch("mg_cxr_kernel"));
     }
     return LAPH_OK;
 }
