@@ -38,12 +38,12 @@ __device__ __forceinline__ void reduce_store(double *v, int nv, double *dst, siz
 // Entries of the slot list this launch walks: the flagged list (built on the
 // device after the rho finalize) in flagged mode, the slot list otherwise.
 __device__ __forceinline__ int blas_count(const BlasArgs &A, int mode) {
-    return mode >= kModeFlagged ? *A.nflist : *A.nlist;
+    return mode == kModeFlagged ? *A.nflist : *A.nlist;
 }
 
 // slot of list entry j, or -1 if it has nothing to do in this mode
 __device__ __forceinline__ int blas_slot_at(const BlasArgs &A, int mode, int j) {
-    const int s = mode >= kModeFlagged ? A.flist[j] : A.list[j];
+    const int s = mode == kModeFlagged ? A.flist[j] : A.list[j];
     const SlotState &st = A.st[s];
     if (mode != kModeAll && st.status != LAPH_RHS_ACTIVE) return -1;
     if (mode == kModeFlagged && st.flag == 0) return -1;
@@ -68,16 +68,15 @@ __device__ __forceinline__ int first_site(const BlasArgs &A) {
     return b * kB;
 }
 
-// p = r + beta (p - omega v) of the active slots, or of those that took a reliable update (where
-// the others' p is updated with their x and r);  beta == 0 means p = r (fresh start: p, v not read).
+// p = r + beta (p - omega v);  beta == 0 means p = r (fresh start: p, v not read).
 // Sites outside A.win are not touched; outside A.win_pv p and v are zero and not read.
 template <class P>
-__global__ __launch_bounds__(kB) void p_update_kernel(BlasArgs A, int mode) {
+__global__ __launch_bounds__(kB) void p_update_kernel(BlasArgs A) {
     using R = typename P::real;
     const int h = first_site(A) + threadIdx.x;
     if (h >= A.vh || !in_window(A.win, h, A.vh)) return;
     const bool zero_pv = !in_window(A.win_pv, h, A.vh);
-    LAPH_FOR_SLOTS(A, mode, s) {
+    LAPH_FOR_SLOTS(A, kModeActive, s) {
         const double2 beta = A.st[s].beta;
         cplx<R> r[12];
         SpinorIO<P>::load(A.r.at(s), A.vh, h, r);
@@ -113,22 +112,36 @@ __global__ __launch_bounds__(kB) void s_update_kernel(BlasArgs A) {
 }
 
 // x_lo += alpha p + omega s (x_lo = ... after a fold or at the start);  r = s - omega t;
-// partials <r^, r>, |r|^2
+// partials <r^, r>, |r|^2.  Outside A.win p, s and t are zero: nothing to do there, except
+// that an x_lo not written since the last fold becomes zero in memory.  r^ is not read where
+// it is zero.
 template <class P, class PX>
 __global__ __launch_bounds__(kB) void xr_update_kernel(BlasArgs A) {
     using R = typename P::real;
     using RX = typename PX::real;
-    const int h = blockIdx.x * kB + threadIdx.x;
+    const int h0 = blockIdx.x * kB, h = h0 + threadIdx.x;
+    const bool outside = block_outside(A.win, h0, min(kB, A.vh - h0), A.vh);   // uniform
+    const bool live = h < A.vh && in_window(A.win, h, A.vh);
+    const bool rh_zero = block_outside(A.win_rh, h0, min(kB, A.vh - h0), A.vh) && *A.rh_full == 0;
     LAPH_FOR_SLOTS(A, kModeActive, s) {
+        // (iters counts this iteration after this kernel)
+        const bool fresh_x = A.st[s].iters < A.st[s].xlo_from;
+        if (!live && h < A.vh && fresh_x) {
+            cplx<RX> x[12];
+#pragma unroll
+            for (int c = 0; c < 12; ++c) x[c] = {RX(0), RX(0)};
+            SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
+        }
+        if (outside) continue;
         double part[3] = {0, 0, 0};
-        if (h < A.vh) {
+        if (live) {
             const cplx<R> al = c_of<R>(A.st[s].alpha), om = c_of<R>(A.st[s].omega);
             cplx<R> p[12], r[12], t[12], rh[12];
             cplx<RX> x[12];
             SpinorIO<P>::load(A.p.at(s), A.vh, h, p);
             SpinorIO<P>::load(A.r.at(s), A.vh, h, r);
             SpinorIO<P>::load(A.t.at(s), A.vh, h, t);
-            if (A.st[s].iters < A.st[s].xlo_from) {   // (iters counts this iteration after this kernel)
+            if (fresh_x) {
 #pragma unroll
                 for (int c = 0; c < 12; ++c) x[c] = {RX(0), RX(0)};
             } else {
@@ -142,81 +155,20 @@ __global__ __launch_bounds__(kB) void xr_update_kernel(BlasArgs A) {
             }
             SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
             SpinorIO<P>::store(A.r.at(s), A.vh, h, r);
-            SpinorIO<P>::load(A.rh.at(s), A.vh, h, rh);
             cplx<R> d = {R(0), R(0)};
             R n2 = R(0);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                cmac_conj(d, rh[c], r[c]);
-                n2 += r[c].re * r[c].re + r[c].im * r[c].im;
+            for (int c = 0; c < 12; ++c) n2 += r[c].re * r[c].re + r[c].im * r[c].im;
+            if (!rh_zero) {
+                SpinorIO<P>::load(A.rh.at(s), A.vh, h, rh);
+#pragma unroll
+                for (int c = 0; c < 12; ++c) cmac_conj(d, rh[c], r[c]);
             }
             part[0] = d.re;
             part[1] = d.im;
             part[2] = n2;
         }
         reduce_store(part, 3, A.partials + (size_t)s * kSolverPq * A.pstride + blockIdx.x, A.pstride);
-    }
-}
-
-// The same with r^ confined to the source's window, and in the same pass,
-// unless a reliable update is about to replace r, p = r + beta (p - omega v).  One pass
-// reads p, s, t, v and x_lo once (504 bytes per site and RHS in FP16N); beta is known
-// before it because rho = <r^, r> = <r^, s> - omega <r^, t> and |r|^2 = |s|^2 - |<t, s>|^2 / |t|^2 come from the sums of the stage that formed t, which reads r^
-// in its window only.  (<r^, s> vanishes by alpha up to rounding; taking it as zero let rho drift
-// from <r^, r>: about one FP16N solve in 400 stalled.  Without a window that stage would read all of r^ for a saving of 2
-// vectors of 23, so other solves keep the two kernels and the direct sums.)
-// Outside A.win p, s and t are zero: nothing to do there, except that an x_lo not written
-// since the last fold becomes zero in memory; outside A.win_pv p and v are zero, not read.
-template <class P, class PX>
-__global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(sizeof(typename P::real) == 4 ? 4 : 2))) void
-xrp_update_kernel(BlasArgs A) {
-    using R = typename P::real;
-    using RX = typename PX::real;
-    const int h = first_site(A) + threadIdx.x;
-    if (h >= A.vh) return;
-    const bool live = in_window(A.win, h, A.vh);
-    const bool zero_pv = !in_window(A.win_pv, h, A.vh);
-    LAPH_FOR_SLOTS(A, kModeActive, s) {
-        const bool fresh_x = A.st[s].iters == A.st[s].xlo_from;
-        if (!live) {
-            if (fresh_x) {
-                cplx<RX> x[12];
-#pragma unroll
-                for (int c = 0; c < 12; ++c) x[c] = {RX(0), RX(0)};
-                SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
-            }
-            continue;
-        }
-        const cplx<R> al = c_of<R>(A.st[s].alpha), om = c_of<R>(A.st[s].omega), be = c_of<R>(A.st[s].beta);
-        cplx<R> p[12], r[12], t[12];
-        SpinorIO<P>::load(A.p.at(s), A.vh, h, p);
-        SpinorIO<P>::load(A.r.at(s), A.vh, h, r);
-        SpinorIO<P>::load(A.t.at(s), A.vh, h, t);
-        {
-            cplx<RX> x[12];
-            if (fresh_x) {
-#pragma unroll
-                for (int c = 0; c < 12; ++c) x[c] = {RX(0), RX(0)};
-            } else {
-                SpinorIO<PX>::load(A.x.at(s), A.vh, h, x);
-            }
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const cplx<R> dx = al * p[c] + om * r[c];
-                x[c] = x[c] + cplx<RX>{RX(dx.re), RX(dx.im)};
-            }
-            SpinorIO<PX>::store(A.x.at(s), A.vh, h, x);
-        }
-#pragma unroll
-        for (int c = 0; c < 12; ++c) r[c] = r[c] - om * t[c];
-        SpinorIO<P>::store(A.r.at(s), A.vh, h, r);
-        if (A.st[s].flag != 0) continue;
-        if (!zero_pv) {
-            SpinorIO<P>::load(A.v.at(s), A.vh, h, t);
-#pragma unroll
-            for (int c = 0; c < 12; ++c) r[c] = r[c] + be * (p[c] - om * t[c]);
-        }
-        SpinorIO<P>::store(A.p.at(s), A.vh, h, r);
     }
 }
 
@@ -330,7 +282,7 @@ __global__ __launch_bounds__(kB) void copy64_kernel(BlasArgs A, Operand dst, Ope
 // table order by one lane.  The flags were written by workgroups of this launch: read past the
 // caches.
 __device__ void flag_tiles(const FinArgs &A) {
-    __shared__ int ks[512], km[512];
+    __shared__ int ks[256], km[256];
     const int nth = blockDim.x;
     const FlagArgs &F = A.flags;
     const int total = *F.ntiles * F.nr;
@@ -380,20 +332,21 @@ __device__ void flag_tiles(const FinArgs &A) {
 // ---------------------------------------------------------------------------
 // Eight independent loads in flight per lane: the partials were just written by
 // workgroups on every XCD, and a loop that waits for each load in turn spends ~0.1 ms
-// of latency per slot and quantity.  The summation order is still fixed.
-// A windowed producer wrote only A.count blocks from A.first on (cyclic).
+// of latency per slot and quantity.  The summation order is fixed.  A windowed producer wrote
+// only `count` blocks from `first` on (cyclic); the others count as the zeros they stand for,
+// each in its place, so a windowed sum has the bits of the whole one.
 __device__ __forceinline__ double wave_sum_partials(const double *p, int first, int count, int nsb) {
     double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    auto at = [&](int i) {
-        const int b = first + i;
-        return p[b < nsb ? b : b - nsb];
+    auto at = [&](int b) {
+        const int d = b - first;
+        return (d < 0 ? d + nsb : d) < count ? p[b] : 0.0;
     };
     int i = threadIdx.x & 63;
-    for (; i + 7 * 64 < count; i += 8 * 64) {
+    for (; i + 7 * 64 < nsb; i += 8 * 64) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) a[k] += at(i + 64 * k);
     }
-    for (; i < count; i += 64) a[0] += at(i);
+    for (; i < nsb; i += 64) a[0] += at(i);
     double s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
@@ -410,12 +363,11 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
 __device__ __forceinline__ bool finite2(double2 a) { return isfinite(a.x) && isfinite(a.y); }
 __device__ __forceinline__ double cabs2(double2 a) { return a.x * a.x + a.y * a.y; }
 
-// end of an iteration: beta from rho_new = rn, and whether a reliable update is due (r2 = |r|^2;
-// finite: a norm that shows NaN and infinities)
-__device__ __forceinline__ void finalize_rho(SlotState &st, double2 rn, double r2, double finite) {
+// end of an iteration: beta from rho_new = rn, and whether a reliable update is due (r2 = |r|^2)
+__device__ __forceinline__ void finalize_rho(SlotState &st, double2 rn, double r2) {
     st.iters += 1;
     st.r2 = r2;
-    if (!isfinite(finite) || !finite2(rn)) st.flag = 2;
+    if (!isfinite(r2) || !finite2(rn)) st.flag = 2;
     if (st.flag != 2) {
         if (cabs2(st.omega) == 0.0 || cabs2(st.rho) == 0.0 || cabs2(rn) == 0.0) {
             st.flag = 2;
@@ -451,7 +403,7 @@ __device__ __forceinline__ void finalize_slot(const FinArgs &A, int what) {
     const double *P = A.partials + (size_t)s * kSolverPq * A.pstride;
     const bool active = st.status == LAPH_RHS_ACTIVE;
     // wave w sums quantity q0 + w (an update's last three: blocks of another kernel) for thread 0
-    __shared__ double v[8];
+    __shared__ double v[4];
     auto sums = [&](int q0) {
         const int w = threadIdx.x >> 6;
         const bool low = what == kFinUpdate && w > 0;
@@ -493,29 +445,7 @@ __device__ __forceinline__ void finalize_slot(const FinArgs &A, int what) {
             if (!active) return;
             sums(0);
             if (threadIdx.x) return;
-            finalize_rho(st, make_double2(v[0], v[1]), v[2], v[2]);
-            return;
-        }
-        case kFinOmegaRho: {
-            // omega = <t, s> / |t|^2 and what r = s - omega t will have: rho = <r^, s> - omega <r^, t>,
-            // |r|^2 = |s|^2 - |<t, s>|^2 / |t|^2; beta; whether a reliable update is due
-            if (!active) return;
-            sums(0);
-            if (threadIdx.x) return;
-            const double2 ts = make_double2(v[0], v[1]), rt = make_double2(v[4], v[5]);
-            const double tt = v[2];
-            double2 rn = make_double2(0, 0);
-            double r2 = v[3];
-            if (!(tt > 0) || !isfinite(tt) || !finite2(ts)) {
-                st.omega = make_double2(0, 0);
-                st.flag = 2;
-            } else {
-                st.omega = make_double2(ts.x / tt, ts.y / tt);
-                const double2 wt = cmul(st.omega, rt);
-                rn = make_double2(v[6] - wt.x, v[7] - wt.y);
-                r2 = fmax(0.0, v[3] - cabs2(ts) / tt);
-            }
-            finalize_rho(st, rn, r2, v[3]);
+            finalize_rho(st, make_double2(v[0], v[1]), v[2]);
             return;
         }
         case kFinUpdate: {
@@ -578,9 +508,9 @@ __device__ __forceinline__ void finalize_slot(const FinArgs &A, int what) {
     }
 }
 
-__global__ __launch_bounds__(512) void finalize_kernel(FinArgs A, int what) {
+__global__ __launch_bounds__(256) void finalize_kernel(FinArgs A, int what) {
     finalize_slot(A, what);
-    if (what != kFinRho && what != kFinOmegaRho) return;
+    if (what != kFinRho) return;
     // the workgroup that finishes last compacts the slots flagged for a reliable update
     __shared__ int last;
     if (threadIdx.x == 0) {
@@ -609,12 +539,11 @@ static dim3 blas_grid(const BlasArgs &a, int mode) {
     return dim3(a.nsb, rows > 0 ? rows : 1);
 }
 
-laph_status blas_p_update(const Ctx &c, const BlasArgs &a, int prec, int mode) {
+laph_status blas_p_update(const Ctx &c, const BlasArgs &a, int prec) {
     BlasArgs w = a;
-    dim3 grid = blas_grid(a, mode == kModeUpdated ? kModeFlagged : mode);
-    grid.x = window_blocks(a.win, kB, a.nsb, a.vh, &w.sb_first);
+    dim3 grid(window_blocks(a.win, kB, a.nsb, a.vh, &w.sb_first), a.nlist_max);
     return dispatch_prec(prec, [&](auto P, auto) {
-        hipLaunchKernelGGL(p_update_kernel<decltype(P)>, grid, dim3(kB), 0, c.stream, w, mode);
+        hipLaunchKernelGGL(p_update_kernel<decltype(P)>, grid, dim3(kB), 0, c.stream, w);
         return check_launch("p_update_kernel");
     });
 }
@@ -631,15 +560,6 @@ laph_status blas_xr_update(const Ctx &c, const BlasArgs &a, int prec) {
     return dispatch_prec(prec, [&](auto P, auto PX) {
         hipLaunchKernelGGL((xr_update_kernel<decltype(P), decltype(PX)>), grid, dim3(kB), 0, c.stream, a);
         return check_launch("xr_update_kernel");
-    });
-}
-laph_status blas_xrp_update(const Ctx &c, const BlasArgs &a, int prec) {
-    BlasArgs w = a;
-    w.sb_first = 0;   // every block: sites outside the window may have an x_lo to clear
-    dim3 grid(a.nsb, a.nlist_max);
-    return dispatch_prec(prec, [&](auto P, auto PX) {
-        hipLaunchKernelGGL((xrp_update_kernel<decltype(P), decltype(PX)>), grid, dim3(kB), 0, c.stream, w);
-        return check_launch("xrp_update_kernel");
     });
 }
 laph_status blas_accumulate(const Ctx &c, const BlasArgs &a, int prec, int mode) {
@@ -669,7 +589,7 @@ laph_status blas_copy64(const Ctx &c, const BlasArgs &a, Operand dst, Operand sr
 laph_status blas_finalize(const Ctx &c, const FinArgs &f, int what) {
     // quantities (= waves) of each step
     const int nq = what == kFinAlpha ? 2 : (what == kFinOmega || what == kFinRho || what == kFinInit) ? 3
-                   : what == kFinOmegaRho ? 8 : what == kFinUpdate ? 4 : 1;
+                   : what == kFinUpdate ? 4 : 1;
     hipLaunchKernelGGL(finalize_kernel, dim3(f.nlist_max), dim3(64 * nq), 0, c.stream, f, what);
     return check_launch("finalize_kernel");
 }

@@ -74,7 +74,7 @@ laph_status launch_stage(const Ctx &c, const StageSpec &s) {
     a.partials = s.partials;
     if (a.ntiles_max <= 0) return LAPH_OK;
     if (s.red && s.pstride < a.nsb) return set_error(LAPH_ERR_INVALID, "partial-sum stride too small");
-    if ((s.red == 1 || s.red == 8) && s.win_w.n > 0 && !s.w_full) return set_error(LAPH_ERR_INVALID, "window of w without its flag");
+    if (s.red == 1 && s.win_w.n > 0 && !s.w_full) return set_error(LAPH_ERR_INVALID, "window of w without its flag");
     bool ok = false;
     if (s.form == kFormLds) {
         if (s.prec == LAPH_F64)

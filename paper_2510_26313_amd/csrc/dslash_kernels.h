@@ -59,7 +59,7 @@ struct StageArgs {
     // LDS form: the launch walks nsb_win site blocks from sb_first (cyclic, in the tiled order); the
     // register form, which serves a few RHS, skips the blocks outside the window
     int nsb_win, sb_first;
-    SiteWindow win_w;        // reductions 1, 8 (LDS form): w is zero outside (not read), unless *w_full
+    SiteWindow win_w;        // reduction 1 (LDS form): w is zero outside (not read), unless *w_full
     const int *w_full;
     // reductions 4 and 5 (FP64 LDS form): the clover term of the output parity and the
     // per-mass diagonal 4 + m0 (|v - A out|^2; a y + b H in - A y2)
@@ -388,7 +388,7 @@ __device__ __forceinline__ void stage_body(const StageArgs &A, int sb, int tile)
     const int p = A.out_parity;
     const int h = sb * kBlock + threadIdx.x;
     const bool valid = h < g.vh && in_window(A.win, h, g.vh);
-    constexpr int NQ = RED == 1 ? 2 : (RED == 2 ? 3 : (RED == 3 ? 1 : (RED == 8 ? 8 : 0)));
+    constexpr int NQ = RED == 1 ? 2 : (RED == 2 ? 3 : (RED == 3 ? 1 : 0));
     double part[NR][NQ > 0 ? NQ : 1];
 #pragma unroll
     for (int r = 0; r < NR; ++r)
@@ -461,7 +461,7 @@ __device__ __forceinline__ void stage_body(const StageArgs &A, int sb, int tile)
                 for (int c = 0; c < 12; ++c) cmac_conj(d, ww[c], res[c]);
                 part[r][0] = (double)d.re;
                 part[r][1] = (double)d.im;
-            } else if (RED == 2 || RED == 8) {
+            } else if (RED == 2) {
                 cplx<R> d = {R(0), R(0)};
                 R n2 = R(0);
 #pragma unroll
@@ -472,25 +472,6 @@ __device__ __forceinline__ void stage_body(const StageArgs &A, int sb, int tile)
                 part[r][0] = (double)d.re;
                 part[r][1] = (double)d.im;
                 part[r][2] = (double)n2;
-                if constexpr (RED == 8) {
-                    R y2n = R(0);
-#pragma unroll
-                    for (int c = 0; c < 12; ++c) y2n += yy[c].re * yy[c].re + yy[c].im * yy[c].im;
-                    cplx<R> ww[12];
-                    SpinorIO<P>::load(A.w.at(slots[r]), g.vh, h, ww);
-                    cplx<R> e = {R(0), R(0)};
-                    d = {R(0), R(0)};
-#pragma unroll
-                    for (int c = 0; c < 12; ++c) {
-                        cmac_conj(d, ww[c], res[c]);
-                        cmac_conj(e, ww[c], yy[c]);
-                    }
-                    part[r][3] = (double)y2n;
-                    part[r][4] = (double)d.re;
-                    part[r][5] = (double)d.im;
-                    part[r][6] = (double)e.re;
-                    part[r][7] = (double)e.im;
-                }
             } else if (RED == 3) {
                 R n2 = R(0);
 #pragma unroll
@@ -554,7 +535,6 @@ inline bool launch_combo(const StageSpec &s, const StageArgs &a, hipStream_t st)
             case 1000: launch_t<P, NR, DAG, true, false, 0, 0, FL>(a, st); return true;     // A^-1 H in
             case 1011: launch_t<P, NR, DAG, true, false, 1, 1, FL>(a, st); return true;     // v = p - A^-1 H t, <r^, v>
             case 1012: launch_t<P, NR, DAG, true, false, 1, 2, FL>(a, st); return true;     // t = s - A^-1 H t, <t,s>,|t|^2
-            case 1018: launch_t<P, NR, DAG, true, false, 1, 8, FL>(a, st); return true;     // same, |s|^2, <r^,t>, <r^,s>
             default: break;
         }
         if constexpr (NR == 1) {

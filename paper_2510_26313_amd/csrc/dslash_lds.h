@@ -127,14 +127,12 @@ __device__ __forceinline__ void stage_lds_body(const StageArgs &A, int sb, int t
     // (v the clover input), 5 out = a y + b H in - A y2 with |out|^2, 6 the hop input is an
     // FP32 half-vector (no reduction), 7 y2 is an FP32 half-vector, added to w as well, with
     // |out|^2
-    // |out|^2; 8: <out, y>, |out|^2, |y|^2, <w, out>, <w, y>
-    constexpr int NQ =
-        RED == 1 ? 2 : (RED == 2 ? 3 : (RED == 8 ? 8 : (RED == 6 ? 0 : (RED >= 3 ? 1 : 0))));
+    constexpr int NQ = RED == 1 ? 2 : (RED == 2 ? 3 : (RED == 6 ? 0 : (RED >= 3 ? 1 : 0)));
     constexpr bool WIDEN_IN = RED == 6, WIDEN_Y2 = RED == 7;
     static_assert(RED != 4 || (CLOVER && POST == 0 && sizeof(R) == 8), "reduction 4: FP64 clover stages");
     static_assert(RED != 5 || (!CLOVER && POST == 2 && sizeof(R) == 8), "reduction 5: FP64 residual stages");
-    static_assert(RED < 6 || RED == 8 || (sizeof(R) == 8 && (RED == 6 ? POST == 0 : POST == 2)), "modes 6, 7: FP64 stages");
-    const bool w_zero = (RED == 1 || RED == 8) && w_is_zero(A, sb * kLdsSites, kLdsSites);   // uniform
+    static_assert(RED < 6 || (sizeof(R) == 8 && (RED == 6 ? POST == 0 : POST == 2)), "modes 6, 7: FP64 stages");
+    const bool w_zero = RED == 1 && w_is_zero(A, sb * kLdsSites, kLdsSites);   // uniform
 #pragma unroll 1
     for (int rw = 0; rw < RW; ++rw) {
         const int slot = A.tile_slots[tile * NT + rw * 4 + wave];
@@ -275,7 +273,7 @@ __device__ __forceinline__ void stage_lds_body(const StageArgs &A, int sb, int t
                     part[0] = d.re;
                     part[1] = d.im;
                 }
-            } else if (RED == 2 || RED == 8) {
+            } else if (RED == 2) {
                 cplx<R> d = {R(0), R(0)};
                 R n2 = R(0);
 #pragma unroll
@@ -286,27 +284,6 @@ __device__ __forceinline__ void stage_lds_body(const StageArgs &A, int sb, int t
                 part[0] = d.re;
                 part[1] = d.im;
                 part[2] = n2;
-                if constexpr (RED == 8) {
-                    R y2n = R(0);
-#pragma unroll
-                    for (int c = 0; c < 12; ++c) y2n += yy[c].re * yy[c].re + yy[c].im * yy[c].im;
-                    part[3] = y2n;
-                    if (!w_zero) {
-                        cplx<R> ww[12];
-                        SpinorIO<P>::load(A.w.at(slot), g.vh, h, ww);
-                        cplx<R> e = {R(0), R(0)};
-                        d = {R(0), R(0)};
-#pragma unroll
-                        for (int c = 0; c < 12; ++c) {
-                            cmac_conj(d, ww[c], res[c]);
-                            cmac_conj(e, ww[c], yy[c]);
-                        }
-                        part[4] = d.re;
-                        part[5] = d.im;
-                        part[6] = e.re;
-                        part[7] = e.im;
-                    }
-                }
             } else if (RED == 3 || RED == 5 || RED == 7) {
                 R n2 = R(0);
 #pragma unroll
@@ -320,8 +297,6 @@ __device__ __forceinline__ void stage_lds_body(const StageArgs &A, int sb, int t
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 double s = part[q];
-                // (the sums with a zero w need no reduction: 4 of 8, 120 instructions of 1500)
-                if (!(RED == 8 && q >= 4 && w_zero))
 #pragma unroll
                 for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
                 if (lane == 0) A.partials[((size_t)slot * A.pq + q) * A.pstride + sb] = s;
@@ -367,7 +342,6 @@ inline bool launch_lds_combo(const StageSpec &s, const StageArgs &a, hipStream_t
         case 1000: launch_lds_t<P, RW, DAG, true, false, 0, 0>(a, st); return true;    // A^-1 H in
         case 1011: launch_lds_t<P, RW, DAG, true, false, 1, 1>(a, st); return true;    // v = p - A^-1 H t, <r^, v>
         case 1012: launch_lds_t<P, RW, DAG, true, false, 1, 2>(a, st); return true;    // t = s - A^-1 H t, <t,s>,|t|^2
-        case 1018: launch_lds_t<P, RW, DAG, true, false, 1, 8>(a, st); return true;    // same, |s|^2, <r^,t>, <r^,s>
         default: break;
     }
     if constexpr (is64) {

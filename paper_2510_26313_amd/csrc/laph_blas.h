@@ -5,12 +5,11 @@
 
 namespace laph {
 
-// slots a vector kernel works on: all, active, flagged for a reliable update, or those of the
-// flagged list that are still active (after the update)
-enum { kModeAll = 0, kModeActive = 1, kModeFlagged = 2, kModeUpdated = 3 };
-enum { kFinAlpha, kFinOmega, kFinRho, kFinOmegaRho, kFinUpdate, kFinInit, kFinBnorm, kFinR64, kFinTrueRes };
+// slots a vector kernel works on: all, active, or flagged for a reliable update
+enum { kModeAll = 0, kModeActive = 1, kModeFlagged = 2 };
+enum { kFinAlpha, kFinOmega, kFinRho, kFinUpdate, kFinInit, kFinBnorm, kFinR64, kFinTrueRes };
 
-constexpr int kSolverPq = 8;   // quantities per slot in the solver's partial sums
+constexpr int kSolverPq = 6;   // quantities per slot in the solver's partial sums
 
 struct BlasArgs {
     int vh = 0;
@@ -26,9 +25,10 @@ struct BlasArgs {
     const int *flist = nullptr;  // flagged mode: slots taking a reliable update
     const int *nflist = nullptr; // device scalar: entries of flist
     SiteWindow win;              // norm2 / copy64: the sources are zero outside it (not read);
-                                 // p / s / xrp updates: the sites updated
+                                 // p / s / x/r updates: the sites updated
+    SiteWindow win_rh;           // x/r update: r^ is zero outside it (not read) unless *rh_full
     int *rh_full = nullptr;      // device flag: r^ is not confined to the source's window (a restart)
-    SiteWindow win_pv;           // p / xrp updates: p and v are zero outside it (not read)
+    SiteWindow win_pv;           // p update: p and v are zero outside it (not read)
     int sb_first = 0;            // first site block of the launch (set by the launcher)
 };
 
@@ -55,13 +55,12 @@ struct FinArgs {
     int first = 0;      // a windowed producer wrote the partials of `count` blocks from `first` (cyclic)
     int count = 0;
     int nsb2 = 0;       // update: blocks of the kernel that wrote quantities 3 .. 5
-    FlagArgs flags;     // rho, omega-rho
+    FlagArgs flags;     // rho
 };
 
-laph_status blas_p_update(const Ctx &c, const BlasArgs &a, int prec, int mode);
+laph_status blas_p_update(const Ctx &c, const BlasArgs &a, int prec);
 laph_status blas_xr_update(const Ctx &c, const BlasArgs &a, int prec);
 laph_status blas_s_update(const Ctx &c, const BlasArgs &a, int prec);
-laph_status blas_xrp_update(const Ctx &c, const BlasArgs &a, int prec);
 laph_status blas_accumulate(const Ctx &c, const BlasArgs &a, int prec, int mode);
 laph_status blas_lower(const Ctx &c, const BlasArgs &a, int prec, int mode, int init);
 laph_status blas_norm2(const Ctx &c, const BlasArgs &a, Operand v1, Operand v2, int mode);

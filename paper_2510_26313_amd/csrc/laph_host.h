@@ -168,7 +168,7 @@ struct StageSpec {
     int pq = 3;                         // quantities per slot
     SiteWindow win;                     // output sites computed (the others untouched; a reduction leaves
                                         // the partials of blocks outside it unwritten)
-    SiteWindow win_w;                   // red == 1, 8: w is zero outside this window (not read there) ...
+    SiteWindow win_w;                   // red == 1: w is zero outside this window (not read there) ...
     const int *w_full = nullptr;        // ... unless this device flag is set
 };
 // site blocks of a stage launch (= partial sums it writes per quantity and slot)

@@ -224,6 +224,7 @@ BlasArgs Solver::blas(int list_max) const {
     a.r64 = ws.E2;
     a.flist = ws.flist;
     a.nflist = ws.nflist;
+    a.win_rh = rh_win;
     a.rh_full = ws.rh_full;
     return a;
 }
@@ -345,7 +346,7 @@ laph_status Solver::stage(int sprec, int out_parity, Operand in, Operand out, in
     s.pstride = pstride;
     s.pq = kSolverPq;
     s.win = win;
-    s.win_w = rh_win;   // reductions 1 and 8: w is r^
+    s.win_w = rh_win;   // reduction 1: w is r^
     s.w_full = ws.rh_full;
     return launch_stage(*c, s);
 }
@@ -392,7 +393,7 @@ FlagArgs Solver::flag_args() const {
 // t0 +- (4 j - 3), v and s live on +- (4 j - 1), t and the new r and p on +- (4 j + 1): the
 // kernels skip the sites beyond, where every vector is exactly zero (tmp is zeroed at the
 // start, p by the first lower, the others are not read there).  The skipped sums are sums of
-// zeros.
+// zeros, so the iterates do not change by a bit.
 laph_status Solver::iteration(int grow) {
     const Operand none;
     BlasArgs a = blas(ns);
@@ -406,28 +407,17 @@ laph_status Solver::iteration(int grow) {
     // s = r - alpha v (in r)
     a.win = wv;
     LAPH_TRY(blas_s_update(*c, a, prec));
+    // t = M_hat s,  <t, s>, |t|^2
     LAPH_TRY(stage(prec, 1, ws.r, ws.tmp, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 0, none, 0, reach(4 * grow)));
-    FinArgs f = fin(ns, nsb_inner, wt, bs);
+    LAPH_TRY(stage(prec, 0, ws.tmp, ws.t, 1, 0, none, 0, 1, ws.r, 1.0, none, 0, -0.25, 2, none, 0, wt));
+    LAPH_TRY(blas_finalize(*c, fin(ns, nsb_inner, wt, bs), kFinOmega));
+    // x_lo += alpha p + omega s;  r = s - omega t;  rho, |r|^2, update decision
     a.win = wt;
     a.win_pv = wv;
-    const bool confined = rh_win.n > 0;   // r^ on the source's window
-    if (confined) {
-        // t = M_hat s,  <t, s>, |t|^2, |s|^2, <r^, t>: omega, rho, beta, |r|^2, the update decision;
-        // x_lo += alpha p + omega s;  r = s - omega t;  p = r + beta (p - omega v) unless flagged
-        LAPH_TRY(stage(prec, 0, ws.tmp, ws.t, 1, 0, none, 0, 1, ws.r, 1.0, none, 0, -0.25, 8, ws.rh, 0, wt));
-        f.flags = flag_args();
-        LAPH_TRY(blas_finalize(*c, f, kFinOmegaRho));
-        LAPH_TRY(blas_xrp_update(*c, a, prec));
-    } else {
-        // t = M_hat s,  <t, s>, |t|^2;  x_lo += alpha p + omega s;  r = s - omega t;  rho, |r|^2, update
-        // decision
-        LAPH_TRY(stage(prec, 0, ws.tmp, ws.t, 1, 0, none, 0, 1, ws.r, 1.0, none, 0, -0.25, 2, none, 0));
-        LAPH_TRY(blas_finalize(*c, f, kFinOmega));
-        LAPH_TRY(blas_xr_update(*c, a, prec));
-        f = fin(ns);
-        f.flags = flag_args();
-        LAPH_TRY(blas_finalize(*c, f, kFinRho));
-    }
+    LAPH_TRY(blas_xr_update(*c, a, prec));
+    FinArgs f = fin(ns, 0, wt, kBlock);
+    f.flags = flag_args();
+    LAPH_TRY(blas_finalize(*c, f, kFinRho));
     BlasArgs u = blas(ns);
     // reliable update of the flagged slots: x64 += x_lo and the FP64 residual of x64.
     // With an FP32 x_lo and the LDS form the residual follows the same exact correction,
@@ -445,7 +435,7 @@ laph_status Solver::iteration(int grow) {
     }
     LAPH_TRY(blas_lower(*c, u, prec, kModeFlagged, 0));
     LAPH_TRY(blas_finalize(*c, fin(ns, nsb64), kFinUpdate));
-    LAPH_TRY(blas_p_update(*c, a, prec, confined ? kModeUpdated : kModeActive));
+    LAPH_TRY(blas_p_update(*c, a, prec));
     return LAPH_OK;
 }
 

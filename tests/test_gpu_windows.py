@@ -30,13 +30,10 @@ def test_light_cone_solves(dims, t0, stencil, prec):
     tile = 4
     p = dict(inner_prec=prec, stencil=stencil, rhs_tile=tile, traversal=2)
     tau, stats = lat.perambulator_raw(V, t0, 0, params=laph.default_params(**p))
-    B = lat.make_sources(V, t0)
-    X, _ = lat.solve_raw(B, 0, params=laph.default_params(**p))
-    _, want = lat.solve_raw(B, 0, params=laph.default_params(**dict(p, inner_prec="f64")))
+    X, want = lat.solve_raw(lat.make_sources(V, t0), 0, params=laph.default_params(**p))
     ref = lat.project_raw(X, V)
     err = float(torch.linalg.vector_norm(tau - ref) / torch.linalg.vector_norm(ref))
     assert err < 1e-8
     assert max(s["true_res"] for s in stats) <= 1e-10
-    # rho and |r|^2 come from other sums than in the general solve: the bound on a mixed-precision
-    # solve's iterations that the parity tests use, the FP64 solver's and three more
-    assert max(s["iters"] for s in stats) <= max(s["iters"] for s in want) + 3
+    # the skipped entries are zeros: the same iterates up to the order of the reductions
+    assert max(s["iters"] for s in stats) <= max(s["iters"] for s in want) + 1
