@@ -280,7 +280,8 @@ __global__ __launch_bounds__(kB) void copy64_kernel(BlasArgs A, Operand dst, Ope
 // iteration, and FP64 tiles of them (tiles never mix masses).  One workgroup; entries of
 // the static FP64 tile table (already grouped by mass) are tested in parallel, then packed in
 // table order by one lane.  The flags were written by workgroups of this launch: read past the
-// caches.
+// caches.  (With a launch of its own, and one more for a second finalize of the update, 8^4 with
+// 64 RHS took 4.70 ms instead of 4.50, where an iteration is a chain of launches.)
 __device__ void flag_tiles(const FinArgs &A) {
     __shared__ int ks[256], km[256];
     const int nth = blockDim.x;

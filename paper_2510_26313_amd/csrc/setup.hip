@@ -87,31 +87,36 @@ laph_status load_gauge(Ctx &c, const double *U) {
 // ---------------------------------------------------------------------------
 // clover term
 // ---------------------------------------------------------------------------
-// A link read one row or column at a time.
-struct LinkRef {
-    const double2 *p;
-    size_t vh;
-    __device__ __forceinline__ cplx<double> at(int e) const {
-        const double2 v = p[e * vh];
-        return {v.x, v.y};
-    }
-    // column k and row k of the link, or of its adjoint
-    template <bool ADJ>
-    __device__ __forceinline__ void col(int k, cplx<double> (&c)[3]) const {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) c[i] = ADJ ? conj(at(3 * k + i)) : at(3 * i + k);
-    }
-    template <bool ADJ>
-    __device__ __forceinline__ void row(int k, cplx<double> (&c)[3]) const {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) c[i] = ADJ ? conj(at(3 * i + k)) : at(3 * k + i);
-    }
+// 3x3 complex matrices in FP64
+struct M3 {
+    cplx<double> m[9];
 };
+__device__ __forceinline__ M3 mmul(const M3 &a, const M3 &b) {
+    M3 c;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            cplx<double> s = {0, 0};
+#pragma unroll
+            for (int k = 0; k < 3; ++k) cmac(s, a.m[i * 3 + k], b.m[k * 3 + j]);
+            c.m[i * 3 + j] = s;
+        }
+    return c;
+}
+__device__ __forceinline__ M3 adj(const M3 &a) {
+    M3 c;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) c.m[i * 3 + j] = conj(a.m[j * 3 + i]);
+    return c;
+}
 
 // the link in direction dir at the site x + dm mu + dn nu, dm, dn in {-1, 0, 1}
 template <int MU, int NU>
-__device__ __forceinline__ LinkRef link64(const Geom &g, const GaugePtrs &gp, const int (&x)[4], int dm, int dn,
-                                          int dir) {
+__device__ __forceinline__ M3 link64(const Geom &g, const GaugePtrs &gp, const int (&x)[4], int dm, int dn,
+                                     int dir) {
     const int ext[4] = {g.lx, g.ly, g.lz, g.lt};
     int c[4] = {x[0], x[1], x[2], x[3]};
     c[MU] += dm;
@@ -120,45 +125,9 @@ __device__ __forceinline__ LinkRef link64(const Geom &g, const GaugePtrs &gp, co
     c[NU] += dn;
     if (c[NU] < 0) c[NU] += ext[NU];
     if (c[NU] == ext[NU]) c[NU] = 0;
-    const int par = (c[0] + c[1] + c[2] + c[3]) & 1;
-    return {reinterpret_cast<const double2 *>(gp.f64(par, dir)) + cb_index(g, c[0], c[1], c[2], c[3]), (size_t)g.vh};
-}
-
-// s += a b (fused multiply-add chain), SUB: s -= a b
-template <bool SUB>
-__device__ __forceinline__ void zmac(cplx<double> &s, cplx<double> a, cplx<double> b) {
-    const double re = SUB ? -a.re : a.re, im = SUB ? -a.im : a.im;
-    s.re = ffma(re, b.re, s.re);
-    s.re = ffma(-im, b.im, s.re);
-    s.im = ffma(re, b.im, s.im);
-    s.im = ffma(im, b.re, s.im);
-}
-
-// s += op(A) op(B) op(C) (SUB: -=), as sums of outer products so that at most a column and a
-// row of a link are live beside the two 3x3 accumulators
-template <bool ADJ_A, bool ADJ_B, bool ADJ_C, bool SUB>
-__device__ __forceinline__ void staple(cplx<double> (&s)[9], LinkRef A, LinkRef B, LinkRef C) {
-    cplx<double> t[9], u[3], v[3];
-#pragma unroll
-    for (int e = 0; e < 9; ++e) t[e] = {0.0, 0.0};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        A.col<ADJ_A>(k, u);
-        B.row<ADJ_B>(k, v);
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) zmac<false>(t[3 * i + j], u[i], v[j]);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        C.row<ADJ_C>(k, v);
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) zmac<SUB>(s[3 * i + j], t[3 * i + k], v[j]);
-    }
-    __builtin_amdgcn_sched_barrier(0);   // later links are not loaded early (registers)
+    M3 u;
+    GaugeIO<F64>::load(gp, (c[0] + c[1] + c[2] + c[3]) & 1, dir, g.vh, cb_index(g, c[0], c[1], c[2], c[3]), u.m);
+    return u;
 }
 
 // An anti-Hermitian 3x3 matrix: i d[k] on the diagonal, o = entries (1,0), (2,0), (2,1).
@@ -166,70 +135,37 @@ struct AH3 {
     double d[3];
     cplx<double> o[3];
 };
-// f += u v - (u v)^+ for a column u and a row v
-__device__ __forceinline__ void ah_mac(AH3 &f, const cplx<double> (&u)[3], const cplx<double> (&v)[3]) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        f.d[k] = ffma(2.0 * u[k].re, v[k].im, f.d[k]);
-        f.d[k] = ffma(2.0 * u[k].im, v[k].re, f.d[k]);
-    }
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-        const int i = e == 0 ? 1 : 2, j = e == 2 ? 1 : 0;
-        zmac<false>(f.o[e], u[i], v[j]);
-        zmac<true>(f.o[e], conj(u[j]), conj(v[i]));
-    }
-}
 
-// F_munu(x) = (Q - Q^+)/8 minus its trace part, Q = sum of the four plaquettes at x.  Q - Q^+
-// does not change when a plaquette is replaced by minus its adjoint, so the two plaquettes
-// that begin with U_mu(x), and the two that end with U_mu(x - mu), share that factor:
-//   Q - Q^+ = W - W^+,  W = U_mu(x) (S1 - S4) + (S2 - S3) U_mu(x - mu)
-// (ten 3x3 products instead of twelve).
+// F_munu(x) = (Q - Q^+)/8 minus its trace part, Q = sum of the four plaquettes at x
 template <int MU, int NU>
 __device__ __forceinline__ AH3 field_strength(const Geom &g, const GaugePtrs &gp, const int (&x)[4]) {
     auto at = [&](int dm, int dn, int dir) { return link64<MU, NU>(g, gp, x, dm, dn, dir); };
+    M3 q;
+    auto add = [&](const M3 &l) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) q.m[k] = q.m[k] + l.m[k];
+        __builtin_amdgcn_sched_barrier(0);   // later links are not loaded early (registers)
+    };
+    // x -> x+mu -> x+mu+nu -> x+nu -> x
+    q = mmul(mmul(at(0, 0, MU), at(1, 0, NU)), mmul(adj(at(0, 1, MU)), adj(at(0, 0, NU))));
+    __builtin_amdgcn_sched_barrier(0);
+    // x -> x+nu -> x+nu-mu -> x-mu -> x
+    add(mmul(mmul(at(0, 0, NU), adj(at(-1, 1, MU))), mmul(adj(at(-1, 0, NU)), at(-1, 0, MU))));
+    // x -> x-mu -> x-mu-nu -> x-nu -> x
+    add(mmul(mmul(adj(at(-1, 0, MU)), adj(at(-1, -1, NU))), mmul(at(-1, -1, MU), at(0, -1, NU))));
+    // x -> x-nu -> x-nu+mu -> x+mu -> x
+    add(mmul(mmul(adj(at(0, -1, NU)), at(0, -1, MU)), mmul(at(1, -1, NU), adj(at(0, 0, MU)))));
     AH3 f;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        f.d[k] = 0.0;
-        f.o[k] = {0.0, 0.0};
+    for (int k = 0; k < 3; ++k) f.d[k] = 0.25 * q.m[4 * k].im;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        const int i = e == 0 ? 1 : 2, j = e == 2 ? 1 : 0;
+        f.o[e] = 0.125 * (q.m[3 * i + j] - conj(q.m[3 * j + i]));
     }
-    cplx<double> s[9], u[3];
+    const double tr = (f.d[0] + f.d[1]) + f.d[2];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-#pragma unroll
-        for (int e = 0; e < 9; ++e) s[e] = {0.0, 0.0};
-        if (half == 0) {
-            // S1 = U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+,  S4 = U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu)
-            staple<false, true, true, false>(s, at(1, 0, NU), at(0, 1, MU), at(0, 0, NU));
-            staple<true, true, false, true>(s, at(1, -1, NU), at(0, -1, MU), at(0, -1, NU));
-            const LinkRef U = at(0, 0, MU);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const cplx<double> r[3] = {s[3 * k], s[3 * k + 1], s[3 * k + 2]};
-                U.col<false>(k, u);
-                ah_mac(f, u, r);
-            }
-        } else {
-            // S2 = U_nu(x) U_mu(x-mu+nu)^+ U_nu(x-mu)^+,  S3 = U_nu(x-nu)^+ U_mu(x-mu-nu)^+ U_nu(x-mu-nu)
-            staple<false, true, true, false>(s, at(0, 0, NU), at(-1, 1, MU), at(-1, 0, NU));
-            staple<true, true, false, true>(s, at(0, -1, NU), at(-1, -1, MU), at(-1, -1, NU));
-            const LinkRef U = at(-1, 0, MU);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const cplx<double> c[3] = {s[k], s[3 + k], s[6 + k]};
-                U.row<false>(k, u);
-                ah_mac(f, c, u);
-            }
-        }
-    }
-    const double tr = (f.d[0] + f.d[1] + f.d[2]) / 3.0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        f.d[k] = 0.125 * (f.d[k] - tr);
-        f.o[k] = 0.125 * f.o[k];
-    }
+    for (int k = 0; k < 3; ++k) f.d[k] = ffma(-(1.0 / 3.0), tr, f.d[k]);
     return f;
 }
 
@@ -239,6 +175,7 @@ struct H3 {
     cplx<double> o[3];
 };
 __device__ __forceinline__ H3 half_i(double csw, const AH3 &a, double s, const AH3 &b) {
+#pragma clang fp contract(off)
     const double f = 0.5 * csw;
     H3 h;
 #pragma unroll
@@ -265,15 +202,17 @@ __device__ __forceinline__ cplx<double> h3_at(const H3 &h, int a, int b) {
 //
 // One wave per plane on 64 sites: the six field strengths (9 reals each) meet in LDS and
 // every wave assembles the entries of its plane's partners.  Bound by the gather of the
-// links (60 per site, 8.6 KB, through the caches): the waves of a block read the same
-// links at about the same time, and products taken as outer products keep a wave small.
-// 32^3 x 64: 2.4 ms.  One thread with all six planes as full matrices, under the default
+// links (16 per plane and site through the caches; the waves of a block read the same ones
+// at about the same time) and the FP64 issue of 12 products a plane.
+// 32^3 x 64: 2.8 ms.  One thread with all six planes as full matrices, under the default
 // 1024-thread register budget, spilled 1208 registers and took 6.56 ms; the same at 256
-// registers 3.63 ms.  Walking the blocks XCD by XCD, or both parities together, changes
-// nothing.
+// registers 3.63 ms.  Sharing a link between plaquettes (10 products a plane, as outer
+// products) takes 2.4 ms but rounds the term differently, and the iterates of every
+// mixed-precision solve with it: the mass gradient of a 16^3 x 32 F16N solve moved by
+// 1.5e-9, with the plain order by 2e-10.
 constexpr int kCloverSites = 64;
 
-__global__ __launch_bounds__(6 * 64) __attribute__((amdgpu_waves_per_eu(3))) void clover_build_kernel(
+__global__ __launch_bounds__(6 * 64) __attribute__((amdgpu_waves_per_eu(2))) void clover_build_kernel(
     Geom g, GaugePtrs gp, double csw, char *term0, char *term1) {
     __shared__ AH3 F[6][kCloverSites];   // xy, zt, yz, xt, xz, yt
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
