@@ -20,11 +20,12 @@
 
 namespace laph {
 
-// Waves per SIMD the register form's kernels are compiled for: its single-RHS FP32 / FP16N
-// tiles need 120-134 registers and are held at the 128 that 4 waves leave; the larger tiles
-// keep their accumulators in up to 512 registers.
-template <class P, int NR>
-constexpr int kStageWaves = NR == 1 && sizeof(typename P::real) == 4 ? 4 : 1;
+// Waves per SIMD the register form's kernels are compiled for: the single-RHS FP16N tiles with
+// the clover term need 128-134 registers and are held at the 128 that 4 waves leave; the plain hop
+// (240, spilling at 128) and the larger tiles keep their accumulators in up to 512 registers, and the
+// FP32 tiles (126) need no bound.
+template <class P, int NR, bool CLOVER>
+constexpr int kStageWaves = NR == 1 && CLOVER && std::is_same_v<P, F16N> ? 4 : 1;
 // The FP64 single-RHS tile serves launches of about one workgroup per CU: scheduled for at
 // most 2 waves per SIMD it keeps more of the gather in flight (16^3 x 32, the stage with
 // <r^, v>: 30.3 us; scheduled for 3 waves 32.5 us).
@@ -496,7 +497,7 @@ __device__ __forceinline__ void stage_body(const StageArgs &A, int sb, int tile)
 }
 
 template <class P, int NR, bool DAG, bool CLOVER, bool PRE, int POST, int RED, bool FLAGGED>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStageWaves<P, NR>, kStageWavesMax<P, NR>))) void stage_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStageWaves<P, NR, CLOVER>, kStageWavesMax<P, NR>))) void stage_kernel(
     StageArgs A) {
     const int nt = *A.ntiles;
     int first, end, step;
