@@ -615,21 +615,17 @@ __global__ __launch_bounds__(kMB) void mg_prolong32_kernel(Geom g, MgDev m, cons
 // coarse operator and coarse BiCGStab (FP64, coarse vectors [n][nc][ncv])
 // ---------------------------------------------------------------------------
 // Scalars of one RHS.  A kernel of the coarse solve has every workgroup read them and its RHS's
-// workgroup 0 write those that no workgroup of that kernel reads (rho alternates); done is
-// written where every workgroup draws the same conclusion from the same sums.
+// workgroup 0 write those that no thread of that launch reads: rho alternates from iteration to
+// iteration, and the p update hands done[0] on to done[1], the s update done[1] to done[0].  So
+// all threads of a launch take the same branches whatever the order its waves run in.
 struct CgState {
     double2 rho[2], alpha, omega;
     double tol2;
-    int done;
+    int done[2];
 };
 
-__device__ __forceinline__ int cg_done(const CgState &s) {
-    return __hip_atomic_load(&s.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void cg_set_done(CgState &s, int done) {
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        __hip_atomic_store(&s.done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// the thread that writes an RHS's scalars
+__device__ __forceinline__ bool cg_writer() { return blockIdx.x == 0 && threadIdx.x == 0; }
 __device__ __forceinline__ double2 cm(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
@@ -651,7 +647,7 @@ __device__ __forceinline__ void cg_mac(double *v, double2 a, double2 b) {
 // 8th column, those of the next step ahead of the products, and keeps the sums of R RHS; of these
 // it ends with one.
 // DOT 1: partial sums <u, out>; 2: <out, u>, <out, out>, [n][3][nc], one per site (u: a coarse
-// vector), so the solve needs no sweep for them.
+// vector), so the solve needs no sweep for them (1 follows the p update and its done, 2 the s update).
 // Bound by latency at small nc: with the blocks staged in LDS per direction (9 serial rounds of
 // load, barrier and LDS reads in the products' chain) coarse 4^3 x 8, 24 components, 8 RHS took
 // 31 us, double-buffered 29 us, now 20 us; its 42 MB take 7 us at the copy rate.  Coarse 8^4: 179 us,
@@ -679,7 +675,7 @@ __global__ __launch_bounds__(kMB) void mg_coarse_apply_kernel(MgDev m, const dou
     const int row = (wave - sub * nw) * 8 + (threadIdx.x >> 3 & 7), cg = threadIdx.x & 7;
     // nothing reads the product of an RHS that is done (each wave looks at all of the workgroup's)
     if constexpr (DOT != 0)
-        if (!__any(!st[first + min((int)(threadIdx.x & 63), all - 1)].done)) return;
+        if (!__any(!st[first + min((int)(threadIdx.x & 63), all - 1)].done[DOT & 1])) return;
     const bool live = row < ncv;
     const double2 *crow = C + (size_t)a * 9 * ncv * ncv + (live ? row : 0) * ncv;
     double2 cc[9], cn[9];
@@ -803,10 +799,10 @@ __global__ __launch_bounds__(kMB) void mg_cinit_kernel(CgState *st, size_t len, 
     }
     block_sum_bcast<3>(v, red);
     if (threadIdx.x < 3) partial[((size_t)rr * 3 + threadIdx.x) * gridDim.x + blockIdx.x] = v[threadIdx.x];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (cg_writer()) {
         CgState &s = st[rr];
         s.rho[1] = s.alpha = s.omega = make_double2(1.0, 0.0);
-        s.done = 0;
+        s.done[0] = 0;
     }
 }
 
@@ -817,16 +813,18 @@ __global__ __launch_bounds__(kMB) void mg_cp_kernel(CgState *st, int it, size_t 
     __shared__ double red[(kMB / 64) * 3];
     const int rr = blockIdx.y;
     CgState &s = st[rr];
-    if (it > 0 && cg_done(s)) return;
+    if (s.done[0]) {
+        if (cg_writer()) s.done[1] = 1;
+        return;
+    }
     double v[3];
     cg_sum(v, partial, rr, np, red);
     const double2 rho = make_double2(v[0], v[1]);
-    if ((it == 0 ? !(v[2] > 0) : v[2] <= s.tol2) || (rho.x == 0 && rho.y == 0)) {
-        cg_set_done(s, 1);
-        return;
-    }
+    const bool done = (it == 0 ? !(v[2] > 0) : v[2] <= s.tol2) || (rho.x == 0 && rho.y == 0);
+    if (cg_writer()) s.done[1] = done;
+    if (done) return;
     const double2 omega = s.omega, beta = cm(cdiv(rho, s.rho[(it + 1) & 1]), cdiv(s.alpha, omega));
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (cg_writer()) {
         s.rho[it & 1] = rho;
         if (it == 0) s.tol2 = tol * tol * v[2];
     }
@@ -844,15 +842,17 @@ __global__ __launch_bounds__(kMB) void mg_cs_kernel(CgState *st, int it, size_t 
     __shared__ double red[(kMB / 64) * 3];
     const int rr = blockIdx.y;
     CgState &s = st[rr];
-    if (cg_done(s)) return;
-    double v[3];
-    cg_sum(v, partial, rr, np, red);
-    if (v[0] == 0 && v[1] == 0) {
-        cg_set_done(s, 1);
+    if (s.done[1]) {
+        if (cg_writer()) s.done[0] = 1;
         return;
     }
+    double v[3];
+    cg_sum(v, partial, rr, np, red);
+    const bool done = v[0] == 0 && v[1] == 0;
+    if (cg_writer()) s.done[0] = done;
+    if (done) return;
     const double2 alpha = cdiv(s.rho[it & 1], make_double2(v[0], v[1]));
-    if (blockIdx.x == 0 && threadIdx.x == 0) s.alpha = alpha;
+    if (cg_writer()) s.alpha = alpha;
     for (size_t i = (size_t)blockIdx.x * kMB + threadIdx.x; i < len; i += (size_t)gridDim.x * kMB) {
         const size_t o = (size_t)rr * len + i;
         const double2 rv = f.r[o], w = cm(alpha, f.v[o]);
@@ -867,13 +867,13 @@ __global__ __launch_bounds__(kMB) void mg_cxr_kernel(CgState *st, size_t len, Cg
     __shared__ double red[(kMB / 64) * 3];
     const int rr = blockIdx.y;
     CgState &s = st[rr];
-    if (cg_done(s)) return;
+    if (s.done[0]) return;
     double v[3];
     cg_sum(v, partial, rr, np, red);
     // t = 0 means s = 0: omega = 0 still takes x += alpha p and r = s
     const double2 alpha = s.alpha;
     const double2 omega = v[2] > 0 ? make_double2(v[0] / v[2], v[1] / v[2]) : make_double2(0.0, 0.0);
-    if (blockIdx.x == 0 && threadIdx.x == 0) s.omega = omega;
+    if (cg_writer()) s.omega = omega;
     double sum[3] = {0.0, 0.0, 0.0};
     for (size_t i = (size_t)blockIdx.x * kMB + threadIdx.x; i < len; i += (size_t)gridDim.x * kMB) {
         const size_t o = (size_t)rr * len + i;
