@@ -32,7 +32,16 @@ static void lds_block_tiles(const Ctx &c, const StageSpec &s, StageArgs &a) {
 laph_status launch_stage(const Ctx &c, const StageSpec &s) {
     StageArgs a;
     a.g = c.g;
-    a.gp = c.gp;
+    if (s.form == kFormLds || s.prec == LAPH_F64) {
+        a.gp = c.gp;
+    } else {
+        for (int k = 0; k < 2; ++k)
+            for (int mu = 0; mu < 4; ++mu) {
+                const int p = k == 0 ? s.out_parity : 1 - s.out_parity;
+                a.lk.a[k][mu] = s.prec == LAPH_F32 ? c.gp.f32(p, mu) : c.gp.f16a(p, mu);
+                a.lk.b[k][mu] = s.prec == LAPH_F32 ? nullptr : c.gp.f16b(p, mu);
+            }
+    }
     a.out_parity = s.out_parity;
     a.in = s.in;
     a.out = s.out;

@@ -20,21 +20,35 @@
 
 namespace laph {
 
-// Waves per SIMD the register form's kernels are compiled for: the single-RHS FP16N tiles with
-// the clover term need 128-134 registers and are held at the 128 that 4 waves leave; the plain hop
-// (240, spilling at 128) and the larger tiles keep their accumulators in up to 512 registers, and the
-// FP32 tiles (126) need no bound.
+// Most waves per SIMD the register form's kernels are scheduled for.  A single-RHS FP16N tile
+// with the clover term takes 115-118 registers at 4, so 4 waves run; left to itself it takes
+// 128-134 (32^4, the stage with <r^, v>: 76.5 us against 72.8), and asked for at least 4 the
+// gather is serialised (76.3 us; the stage without it 61.2 against 56.0).  The FP64 single-RHS
+// tile keeps more of the gather in flight scheduled for 2 (16^3 x 32, the stage with <r^, v>: 30.3 us;
+// for 3 waves 32.5 us).
 template <class P, int NR, bool CLOVER>
-constexpr int kStageWaves = NR == 1 && CLOVER && std::is_same_v<P, F16N> ? 4 : 1;
-// The FP64 single-RHS tile serves launches of about one workgroup per CU: scheduled for at
-// most 2 waves per SIMD it keeps more of the gather in flight (16^3 x 32, the stage with
-// <r^, v>: 30.3 us; scheduled for 3 waves 32.5 us).
-template <class P, int NR>
-constexpr int kStageWavesMax = NR == 1 && sizeof(typename P::real) == 8 ? 2 : 8;
+constexpr int kStageWavesMax = NR != 1                       ? 8
+                               : sizeof(typename P::real) == 8 ? 2
+                               : CLOVER && std::is_same_v<P, F16N> ? 4
+                                                                   : 8;
+
+// Link arrays of a launch of the register form in 32 bits, of its precision alone: [0 output
+// parity, 1 the other][mu].  Addresses at fixed places among the arguments cost a scalar load; by
+// base + size they are computed for every hop and kept in registers that spill (FP16N, one RHS,
+// the two stages on 32^4: 63.4 and 76.6 us, by pointer 56.0 and 72.8; two RHS tile by tile 101 and
+// 118, now 85.4 and 103; FP32 within 1 %).  In FP64, and in the LDS form, where a wave's direction is
+// not a constant, base + size is the faster one (FP64 by 1 %; LDS, 32^3 x 64, one RHS FP16N:
+// 187 us, by pointers 202).
+struct LinkPtrs {
+    const char *a[2][4], *b[2][4];   // b: FP16N
+};
 
 struct StageArgs {
     Geom g;
-    GaugePtrs gp;
+    union {
+        GaugePtrs gp;    // LDS form, and FP64
+        LinkPtrs lk;     // register form, FP32 and FP16N
+    };
     int out_parity;
     Operand in, out, y, y2, z, w;
     double a, a2, b, c;
@@ -315,10 +329,10 @@ __device__ __forceinline__ void hop_dir(const StageArgs &A, int p, int h, const 
     const R eta = (MU == 3 && wrap && g.antiperiodic) ? R(-1) : R(1);
     const int hn = cb_index(g, n[0], n[1], n[2], n[3]);
     cplx<R> L[9];
-    if (FWD)
-        GaugeIO<P>::load(A.gp, p, MU, g.vh, h, L);
+    if constexpr (sizeof(R) == 8)
+        GaugeIO<P>::load(A.gp, FWD ? p : 1 - p, MU, g.vh, FWD ? h : hn, L);
     else
-        GaugeIO<P>::load(A.gp, 1 - p, MU, g.vh, hn, L);
+        GaugeIO<P>::load(A.lk.a[FWD ? 0 : 1][MU], A.lk.b[FWD ? 0 : 1][MU], g.vh, FWD ? h : hn, L);
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         if (slots[r] < 0) continue;
@@ -497,7 +511,7 @@ __device__ __forceinline__ void stage_body(const StageArgs &A, int sb, int tile)
 }
 
 template <class P, int NR, bool DAG, bool CLOVER, bool PRE, int POST, int RED, bool FLAGGED>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStageWaves<P, NR, CLOVER>, kStageWavesMax<P, NR>))) void stage_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, kStageWavesMax<P, NR, CLOVER>))) void stage_kernel(
     StageArgs A) {
     const int nt = *A.ntiles;
     int first, end, step;

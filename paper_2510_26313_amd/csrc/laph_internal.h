@@ -323,7 +323,6 @@ struct SpinorIO<F16N> {
 // ---------------------------------------------------------------------------
 struct GaugePtrs {
     // base and size of the per-(parity, mu) arrays of each format, (parity, mu) = (0,0), (0,1), ...
-    // (addresses by arithmetic: tables of 32 pointers were a third of the stencil's arguments)
     const char *b64, *b32, *b16a, *b16b;
     size_t s64, s32, s16a, s16b;
     __host__ __device__ const char *f64(int p, int mu) const { return b64 + (p * 4 + mu) * s64; }
@@ -343,11 +342,15 @@ __device__ __forceinline__ void reconstruct_row2(cplx<R> (&u)[9]) {
 template <class P>
 struct GaugeIO;
 
+// load from the array a (F16N: and b) of one (parity, mu), or by parity and direction
 template <>
 struct GaugeIO<F64> {
     static __device__ __forceinline__ void load(const GaugePtrs &g, int parity, int mu, int vh, int h,
                                                 cplx<double> (&u)[9]) {
-        const double2 *p = reinterpret_cast<const double2 *>(g.f64(parity, mu));
+        load(g.f64(parity, mu), nullptr, vh, h, u);
+    }
+    static __device__ __forceinline__ void load(const char *a, const char *, int vh, int h, cplx<double> (&u)[9]) {
+        const double2 *p = reinterpret_cast<const double2 *>(a);
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
             double2 v = p[(size_t)k * vh + h];
@@ -360,7 +363,10 @@ template <>
 struct GaugeIO<F32> {
     static __device__ __forceinline__ void load(const GaugePtrs &g, int parity, int mu, int vh, int h,
                                                 cplx<float> (&u)[9]) {
-        const float4 *p = reinterpret_cast<const float4 *>(g.f32(parity, mu));
+        load(g.f32(parity, mu), nullptr, vh, h, u);
+    }
+    static __device__ __forceinline__ void load(const char *a, const char *, int vh, int h, cplx<float> (&u)[9]) {
+        const float4 *p = reinterpret_cast<const float4 *>(a);
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             float4 v = p[(size_t)j * vh + h];
@@ -375,8 +381,11 @@ template <>
 struct GaugeIO<F16N> {
     static __device__ __forceinline__ void load(const GaugePtrs &g, int parity, int mu, int vh, int h,
                                                 cplx<float> (&u)[9]) {
-        half8 a = reinterpret_cast<const half8 *>(g.f16a(parity, mu))[h];
-        half4 b = reinterpret_cast<const half4 *>(g.f16b(parity, mu))[h];
+        load(g.f16a(parity, mu), g.f16b(parity, mu), vh, h, u);
+    }
+    static __device__ __forceinline__ void load(const char *pa, const char *pb, int vh, int h, cplx<float> (&u)[9]) {
+        half8 a = reinterpret_cast<const half8 *>(pa)[h];
+        half4 b = reinterpret_cast<const half4 *>(pb)[h];
 #pragma unroll
         for (int k = 0; k < 4; ++k) u[k] = {(float)a[2 * k], (float)a[2 * k + 1]};
         u[4] = {(float)b[0], (float)b[1]};
