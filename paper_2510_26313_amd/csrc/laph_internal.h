@@ -176,6 +176,12 @@ inline SiteWindow slab_window(const Geom &g, int t0, int k) {
     return w;
 }
 
+// the timeslices the residual lives on at the start of a solve pass: t0 +- 1 for a source on
+// timeslice t0 alone; with an x to start from (a warm start, a later pass) M_hat x fills the lattice
+inline SiteWindow first_residual_window(const Geom &g, bool one_timeslice, int t0, bool have_x) {
+    return one_timeslice && !have_x ? slab_window(g, t0, 1) : SiteWindow();
+}
+
 // ---------------------------------------------------------------------------
 // precisions
 // ---------------------------------------------------------------------------

@@ -565,8 +565,9 @@ laph_status Solver::solve(const SourceSpec &src, const std::vector<int> &slot_ma
         }
         // partials of the FP64 stage (warm start) or of the norm kernel
         LAPH_TRY(blas_finalize(*c, have_x ? fin(ncur, nsb64) : f, kFinR64));
-        // r^ = r: the slab of b_hat on the first pass, the whole lattice on the others
-        LAPH_TRY(blas_lower(*c, a, prec, kModeActive, pass == 0 ? 1 : 2));
+        // r^ = r: on the slab of b_hat, or the whole lattice
+        const bool confined = first_residual_window(c->g, slab, src.t0, have_x).n > 0;
+        LAPH_TRY(blas_lower(*c, a, prec, kModeActive, confined ? 1 : 2));
         LAPH_TRY(blas_finalize(*c, f, kFinInit));
         // iterate; the captured graph always spans ns slots (tables say which are live)
         LAPH_TRY(download_state());
@@ -581,7 +582,7 @@ laph_status Solver::solve(const SourceSpec &src, const std::vector<int> &slot_ma
         // on its slab and the shared finalizes: 32^3 x 64, 48 RHS FP16N 789 -> 700 ms; 16^3 x 32,
         // 160 RHS 153 -> 144 ms)
         int grow = 0;
-        if (slab && pass == 0 && (size_t)c->g.vh * ncur >= ((size_t)1 << 20))
+        if (confined && (size_t)c->g.vh * ncur >= ((size_t)1 << 20))
             while (2 * (4 * (grow + 1) - 2) + 1 < c->g.lt) ++grow;
         if (grow > 0) LAPH_HIP(hipMemsetAsync(ws.tmp.base, 0, ws.tmp.stride * n, c->stream));
         int guard = 0;
