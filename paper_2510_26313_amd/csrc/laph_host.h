@@ -33,9 +33,6 @@ struct SlotState {
                       // stale, not read) before it
 };
 
-constexpr int kBlock = 256;     // sites per workgroup of the register form and of the vector kernels
-constexpr int kLdsSites = 64;   // sites per workgroup of the LDS form
-
 // Two forms of the stencil stage kernel: RHS tiles held in registers by one
 // thread, or RHS-parallel waves sharing links staged in LDS.
 enum { kFormRegister = 0, kFormLds = 1 };

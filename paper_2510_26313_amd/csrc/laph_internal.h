@@ -154,6 +154,9 @@ __host__ __device__ inline bool block_outside(const SiteWindow &w, int h0, int c
     return d >= w.n && d + cnt <= vh;
 }
 
+constexpr int kBlock = 256;     // sites per workgroup of the register form and of the vector kernels
+constexpr int kLdsSites = 64;   // sites per workgroup of the LDS form
+
 // the blocks of `size` consecutive sites (nb in all) that overlap the window: a cyclic range
 // of block indices from *first; every block when it covers the lattice
 inline int window_blocks(const SiteWindow &w, int size, int nb, int vh, int *first) {
