@@ -28,6 +28,7 @@
 #include <cmath>
 #include <vector>
 
+#include "contract_plan.h"
 #include "laph_solver.h"
 
 namespace laph {
@@ -35,13 +36,12 @@ namespace laph {
 namespace {
 
 constexpr int kCB = 256;          // threads per workgroup (4 waves)
-constexpr int kCS = 8;            // sites per K chunk
+constexpr int kCS = kPlanSites;   // sites per K chunk
 constexpr int kCK = 3 * kCS;      // K (site, colour) per chunk
 constexpr int kRS = kCK + 1;      // LDS row stride in complex (odd: conflict-free fragment reads)
 constexpr int kSlots = 64 * kRS;  // complex slots of one staged chunk (64 rows)
 constexpr int kCRows = 64;        // l rows: nev <= 64
-constexpr int kCMaxMom = 16;      // momenta per launch
-constexpr int kCTarget = 2048;    // workgroups aimed for by the K split
+constexpr int kCMaxMom = kPlanMaxMom;   // momenta per launch
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
@@ -378,7 +378,7 @@ __global__ void triplet_reduce_kernel(ContractArgs A, double2 *B) {
 // Doublets by planes: Phi of up to kPlaneMom momenta of one (px, py) from S(z).  A member with
 // flip has the opposite (px, py): Phi_p[m][l] = conj(sum_z e^{+i pz z} S(z)[l][m]).  herm: S(z)
 // holds the blocks on and above the diagonal and its other half follows the same way.
-constexpr int kPlaneMom = 8;
+constexpr int kPlaneMom = kPlanPlaneMom;
 constexpr int kPlaneZ = 128;   // phases kept in LDS
 
 struct PlaneArgs {
@@ -448,7 +448,7 @@ void contract_shape(const Ctx &c, int kind, int nev, int nmom, ContractArgs &a) 
     a.nmom = nmom;
     a.nchunk = (a.vs + kCS - 1) / kCS;
     const int base = a.lt * a.ntile * nmom;
-    a.nsplit = std::max(1, std::min({(kCTarget + base - 1) / base, a.nchunk, 64}));
+    a.nsplit = plan_split(base, a.nchunk);
 }
 
 }  // namespace
@@ -481,16 +481,6 @@ struct PlaneGroup {
     int px, py, herm;
     std::vector<int> members, flip;
 };
-
-// Doublets by planes pay when the products they save outweigh the extra launches (about
-// 10 us) and the pass over S(z): a plane of 64 sites costs as much as writing and reading
-// its S(z) five times, and one momentum's products run at about 50 TFLOP/s.
-static bool planes_pay(const Ctx &c, int nev, const PlaneGroup &g) {
-    if (c.g.lx * c.g.ly < 64) return false;
-    const double saved = (double)g.members.size() - (g.herm ? 0.625 : 1.0);
-    const double one = 8.0 * 6.0 * c.g.vh * nev * nev / 50e12;   // seconds per momentum
-    return saved * one > 40e-6;
-}
 
 static std::vector<PlaneGroup> plane_groups(const Ctx &c, int n_mom, const int *mom) {
     std::vector<PlaneGroup> gs;
@@ -568,11 +558,16 @@ laph_status contract(const Ctx &c, int kind, double *out, const double *V, int n
     // does not pay by planes
     std::vector<int> rest;
     if (kind == 0) {
+        const DoubletPlan plan{c.g.lx, c.g.ly, c.g.lz, c.g.lt, nev};
+        int n_left = n_mom;
         for (const PlaneGroup &g : plane_groups(c, n_mom, mom_host)) {
-            if (planes_pay(c, nev, g))
+            const int n = (int)g.members.size();
+            if (plan.by_planes(n, g.herm, n_left)) {
                 LAPH_TRY(doublet_planes(c, g, out, V, nev, mom_host, work));
-            else
+                n_left -= n;
+            } else {
                 rest.insert(rest.end(), g.members.begin(), g.members.end());
+            }
         }
     } else {
         for (int q = 0; q < n_mom; ++q) rest.push_back(q);
