@@ -448,7 +448,7 @@ void contract_shape(const Ctx &c, int kind, int nev, int nmom, ContractArgs &a) 
     a.nmom = nmom;
     a.nchunk = (a.vs + kCS - 1) / kCS;
     const int base = a.lt * a.ntile * nmom;
-    a.nsplit = plan_split(base, a.nchunk);
+    a.nsplit = kind == 0 ? plan_split(base, a.nchunk) : triplet_split(base, a.nchunk);
 }
 
 }  // namespace

@@ -17,6 +17,14 @@ inline int plan_split(int base, int nchunk) {
     return std::max(1, std::min({(kPlanTarget + base - 1) / base, nchunk, kPlanMaxSplit}));
 }
 
+// The same for triplets, with at least 4 chunks a slice (and 4 slices where there are chunks): a
+// slice's entry is written once and read for six orderings, which takes about what the products
+// of 4 chunks on it take.  8^4 (64 chunks), 33 and 48 vectors, two and one momenta: 262 and 352 us with
+// a chunk a slice, 116 and 156 now; 4^4 (8 chunks) is fastest with 4 slices, 12^3 x 24 and above as before.
+inline int triplet_split(int base, int nchunk) {
+    return plan_split(base, std::max(std::min(nchunk, 4), nchunk / 4));
+}
+
 // Products at 50 TFLOP/s, slices or planes written and read at 5 TB/s, 20 us a launch: with these
 // no group of 1 to 8 momenta on 40 lattices from 8^4 to 32^3 x 64, nev 4 to 64, was sent the way that
 // was more than 3 % slower than the whole phase.
