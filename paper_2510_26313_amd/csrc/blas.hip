@@ -193,14 +193,15 @@ __global__ __launch_bounds__(kB) void accumulate_kernel(BlasArgs A, int mode) {
 
 // r = lo(r64); restart (flag 2) or init: r^ = r; init: p = r.  init 1: r lives on the source's
 // window, 2: on the whole lattice.
-// partials <r^, r>, |r|^2
-template <class P, class PX>
+// partials <r^, r>, |r|^2.  INIT is init != 0: the update's form, launched every iteration and mostly
+// with little to do, has no p to store and a third fewer registers.
+template <class P, class PX, bool INIT>
 __global__ __launch_bounds__(kB) void lower_kernel(BlasArgs A, int mode, int init) {
     using R = typename P::real;
     const int h = blockIdx.x * kB + threadIdx.x;
     LAPH_FOR_SLOTS(A, mode, s) {
         // a restart replaces r^: it is no longer confined to the source's window
-        if ((init || A.st[s].flag == 2) && blockIdx.x == 0 && threadIdx.x == 0) *A.rh_full = init != 1;
+        if ((INIT || A.st[s].flag == 2) && blockIdx.x == 0 && threadIdx.x == 0) *A.rh_full = init != 1;
         double part[3] = {0, 0, 0};
         if (h < A.vh) {
             cplx<double> y[12];
@@ -211,8 +212,8 @@ __global__ __launch_bounds__(kB) void lower_kernel(BlasArgs A, int mode, int ini
             SpinorIO<P>::store(A.r.at(s), A.vh, h, r);
             // work with the stored (rounded) values so r^ and r agree exactly
             SpinorIO<P>::load(A.r.at(s), A.vh, h, r);
-            const bool reset = init || A.st[s].flag == 2;
-            if (init) SpinorIO<P>::store(A.p.at(s), A.vh, h, r);
+            const bool reset = INIT || A.st[s].flag == 2;
+            if constexpr (INIT) SpinorIO<P>::store(A.p.at(s), A.vh, h, r);
             if (reset) {
                 SpinorIO<P>::store(A.rh.at(s), A.vh, h, r);
                 SpinorIO<P>::load(A.rh.at(s), A.vh, h, rh);
@@ -449,6 +450,14 @@ __device__ __forceinline__ void finalize_slot(const FinArgs &A, int what) {
             finalize_rho(st, make_double2(v[0], v[1]), v[2]);
             return;
         }
+        case kFinUpdateRho: {
+            if (!(active && st.flag != 0)) return;
+            sums(3);
+            if (threadIdx.x) return;
+            finalize_residual(st, make_double2(v[0], v[1]), v[2], st.flag == 2);
+            return;
+        }
+        case kFinUpdateNorm:
         case kFinUpdate: {
             // after a reliable update: r2_upd = |b_hat - M x64|^2, whether the slot is done, and rho and
             // beta from the corrected residual r = lo(r64)
@@ -469,7 +478,7 @@ __device__ __forceinline__ void finalize_slot(const FinArgs &A, int what) {
                 st.restarts += 1;
                 if (st.restarts > A.max_restarts) st.status = LAPH_RHS_BREAKDOWN;
             }
-            if (st.status != LAPH_RHS_ACTIVE) return;
+            if (st.status != LAPH_RHS_ACTIVE || what == kFinUpdateNorm) return;
             finalize_residual(st, make_double2(v[1], v[2]), v[3], st.flag == 2);
             return;
         }
@@ -573,7 +582,10 @@ laph_status blas_accumulate(const Ctx &c, const BlasArgs &a, int prec, int mode)
 laph_status blas_lower(const Ctx &c, const BlasArgs &a, int prec, int mode, int init) {
     dim3 grid = blas_grid(a, mode);
     return dispatch_prec(prec, [&](auto P, auto PX) {
-        hipLaunchKernelGGL((lower_kernel<decltype(P), decltype(PX)>), grid, dim3(kB), 0, c.stream, a, mode, init);
+        if (init)
+            hipLaunchKernelGGL((lower_kernel<decltype(P), decltype(PX), true>), grid, dim3(kB), 0, c.stream, a, mode, init);
+        else
+            hipLaunchKernelGGL((lower_kernel<decltype(P), decltype(PX), false>), grid, dim3(kB), 0, c.stream, a, mode, 0);
         return check_launch("lower_kernel");
     });
 }
@@ -589,7 +601,8 @@ laph_status blas_copy64(const Ctx &c, const BlasArgs &a, Operand dst, Operand sr
 }
 laph_status blas_finalize(const Ctx &c, const FinArgs &f, int what) {
     // quantities (= waves) of each step
-    const int nq = what == kFinAlpha ? 2 : (what == kFinOmega || what == kFinRho || what == kFinInit) ? 3
+    const int nq = what == kFinAlpha ? 2
+                   : (what == kFinOmega || what == kFinRho || what == kFinUpdateRho || what == kFinInit) ? 3
                    : what == kFinUpdate ? 4 : 1;
     hipLaunchKernelGGL(finalize_kernel, dim3(f.nlist_max), dim3(64 * nq), 0, c.stream, f, what);
     return check_launch("finalize_kernel");

@@ -7,7 +7,8 @@ namespace laph {
 
 // slots a vector kernel works on: all, active, or flagged for a reliable update
 enum { kModeAll = 0, kModeActive = 1, kModeFlagged = 2 };
-enum { kFinAlpha, kFinOmega, kFinRho, kFinUpdate, kFinInit, kFinBnorm, kFinR64, kFinTrueRes };
+// (kFinUpdate: kFinUpdateNorm and kFinUpdateRho at once)
+enum { kFinAlpha, kFinOmega, kFinRho, kFinUpdate, kFinUpdateNorm, kFinUpdateRho, kFinInit, kFinBnorm, kFinR64, kFinTrueRes };
 
 constexpr int kSolverPq = 6;   // quantities per slot in the solver's partial sums
 

@@ -433,8 +433,17 @@ laph_status Solver::iteration(int grow) {
         LAPH_TRY(stage(LAPH_F64, 1, ws.E1, ws.O0, 1, 0, none, 0, 0, none, 0, none, 0, 1.0, 0, none, 1));
         LAPH_TRY(stage(LAPH_F64, 0, ws.O0, ws.E2, 1, 0, none, 0, 2, ws.E0, 1.0, ws.E1, -1.0, 0.25, 3, none, 1));
     }
-    LAPH_TRY(blas_lower(*c, u, prec, kModeFlagged, 0));
-    LAPH_TRY(blas_finalize(*c, fin(ns, nsb64), kFinUpdate));
+    // one finalize for both sums saves a launch an iteration, but then r of an RHS that is done is
+    // formed for nothing, so two from 2^22 site-RHS on (24^3 x 48, 40 RHS FP32: 311 ms with one, 304 with
+    // two; 32^4, 16 RHS FP64: 382 and 367; 16^3 x 32 with 12 to 64 RHS: no difference)
+    if ((size_t)c->g.vh * ns >= ((size_t)1 << 22)) {
+        LAPH_TRY(blas_finalize(*c, fin(ns, nsb64), kFinUpdateNorm));
+        LAPH_TRY(blas_lower(*c, u, prec, kModeFlagged, 0));
+        LAPH_TRY(blas_finalize(*c, fin(ns), kFinUpdateRho));
+    } else {
+        LAPH_TRY(blas_lower(*c, u, prec, kModeFlagged, 0));
+        LAPH_TRY(blas_finalize(*c, fin(ns, nsb64), kFinUpdate));
+    }
     LAPH_TRY(blas_p_update(*c, a, prec));
     return LAPH_OK;
 }
