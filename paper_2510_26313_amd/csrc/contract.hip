@@ -558,16 +558,15 @@ laph_status contract(const Ctx &c, int kind, double *out, const double *V, int n
     // does not pay by planes
     std::vector<int> rest;
     if (kind == 0) {
-        const DoubletPlan plan{c.g.lx, c.g.ly, c.g.lz, c.g.lt, nev};
-        int n_left = n_mom;
-        for (const PlaneGroup &g : plane_groups(c, n_mom, mom_host)) {
-            const int n = (int)g.members.size();
-            if (plan.by_planes(n, g.herm, n_left)) {
-                LAPH_TRY(doublet_planes(c, g, out, V, nev, mom_host, work));
-                n_left -= n;
-            } else {
-                rest.insert(rest.end(), g.members.begin(), g.members.end());
-            }
+        const std::vector<PlaneGroup> groups = plane_groups(c, n_mom, mom_host);
+        std::vector<std::pair<int, bool>> sizes;
+        for (const PlaneGroup &g : groups) sizes.push_back({(int)g.members.size(), g.herm != 0});
+        const std::vector<char> by = DoubletPlan{c.g.lx, c.g.ly, c.g.lz, c.g.lt, nev}.by_planes(sizes);
+        for (size_t k = 0; k < groups.size(); ++k) {
+            if (by[k])
+                LAPH_TRY(doublet_planes(c, groups[k], out, V, nev, mom_host, work));
+            else
+                rest.insert(rest.end(), groups[k].members.begin(), groups[k].members.end());
         }
     } else {
         for (int q = 0; q < n_mom; ++q) rest.push_back(q);

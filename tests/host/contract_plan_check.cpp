@@ -1,12 +1,21 @@
-// Reads "lx ly lz lt nev n herm n_left" lines, prints whether the doublets of n momenta of one
-// (px, py) go by planes.
+// Reads "lx ly lz lt nev groups", then "momenta herm" of each group; prints how many groups of doublets
+// go by planes.
 #include <cstdio>
 
 #include "../../paper_2510_26313_amd/csrc/contract_plan.h"
 
 int main() {
-    int lx, ly, lz, lt, nev, n, herm, left;
-    while (std::scanf("%d %d %d %d %d %d %d %d", &lx, &ly, &lz, &lt, &nev, &n, &herm, &left) == 8)
-        std::printf("%d\n", (int)laph::DoubletPlan{lx, ly, lz, lt, nev}.by_planes(n, herm != 0, left));
+    int lx, ly, lz, lt, nev, n;
+    while (std::scanf("%d %d %d %d %d %d", &lx, &ly, &lz, &lt, &nev, &n) == 6) {
+        std::vector<std::pair<int, bool>> groups;
+        for (int k = 0; k < n; ++k) {
+            int m, h;
+            if (std::scanf("%d %d", &m, &h) != 2) return 1;
+            groups.push_back({m, h != 0});
+        }
+        int by = 0;
+        for (char c : laph::DoubletPlan{lx, ly, lz, lt, nev}.by_planes(groups)) by += c;
+        std::printf("%d\n", by);
+    }
     return 0;
 }

@@ -1,7 +1,7 @@
 """The rule that sends doublets by planes, against times of both ways measured on an MI355X (us, one
 call): few planes leave the chip idle, a workgroup count just above a multiple of the 256 CUs
-costs a whole round, a Hermitian plane alone saves little, and small nev takes the time of a
-16-block."""
+costs a whole round, a Hermitian plane alone saves little, small nev takes the time of a
+16-block, and what a group saves depends on the momenta that stay."""
 import os
 import shutil
 import subprocess
@@ -21,13 +21,22 @@ MEASURED = [
 ]
 
 
+# the same for several groups: (momenta, Hermitian) of each, and all of them one way or the other
+SEVERAL = [
+    ((8, 8, 16, 32, 64), [(2, 1), (2, 0), (2, 0), (2, 0)], 549, 335),
+    ((32, 32, 8, 8, 8), [(3, 1), (6, 0), (6, 0), (6, 0), (6, 0)], 1061, 1275),
+    ((12, 12, 12, 24, 64), [(2, 1), (2, 0), (2, 0), (2, 0)], 729, 615),
+]
+
+
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
 def test_rule_takes_the_faster_way(tmp_path):
     exe = str(tmp_path / "check")
     r = subprocess.run(["g++", "-std=c++17", "-O1", os.path.join(ROOT, "tests", "host", "contract_plan_check.cpp"),
                         "-o", exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr[-4000:]
-    lines = "".join("%d %d %d %d %d %d %d %d\n" % (m[:7] + (m[5],)) for m in MEASURED)
+    cases = [(m[:5], [m[5:7]], m[7], m[8]) for m in MEASURED] + SEVERAL
+    lines = "".join("%d %d %d %d %d %d %s\n" % (d + (len(g), " ".join("%d %d" % x for x in g))) for d, g, _, _ in cases)
     r = subprocess.run([exe], input=lines, capture_output=True, text=True, timeout=60)
     assert r.returncode == 0
-    assert [int(v) for v in r.stdout.split()] == [int(m[8] < m[7]) for m in MEASURED]
+    assert [int(v) for v in r.stdout.split()] == [len(g) if planes < whole else 0 for _, g, whole, planes in cases]
