@@ -204,9 +204,9 @@ __device__ __forceinline__ cplx<double> h3_at(const H3 &h, int a, int b) {
 // every wave assembles the entries of its plane's partners.  Bound by the gather of the
 // links (16 per plane and site through the caches; the waves of a block read the same ones
 // at about the same time) and the FP64 issue of 12 products a plane.
-// 32^3 x 64: 2.8 ms.  One thread with all six planes as full matrices, under the default
-// 1024-thread register budget, spilled 1208 registers and took 6.56 ms; the same at 256
-// registers 3.63 ms.  Sharing a link between plaquettes (10 products a plane, as outer
+// 32^3 x 64: 2.2-2.4 ms in a kernel trace (2.8 when the next figures were taken).  One thread
+// with all six planes as full matrices, under the default 1024-thread register budget, spilled
+// 1208 registers and took 6.56 ms; the same at 256 registers 3.63 ms.  Sharing a link between plaquettes (10 products a plane, as outer
 // products) takes 2.4 ms but rounds the term differently, and the iterates of every
 // mixed-precision solve with it: the mass gradient of a 16^3 x 32 F16N solve moved by
 // 1.5e-9, with the plain order by 2e-10.
