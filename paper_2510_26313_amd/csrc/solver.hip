@@ -588,8 +588,8 @@ laph_status Solver::solve(const SourceSpec &src, const std::vector<int> &slot_ma
         // iterations whose vectors do not reach the whole lattice yet run as plain launches on
         // their windows, where that pays: below about 2^20 site-RHS an iteration takes less
         // than 0.5 ms, about 20 launches of 5 us, and the graph's replay is as fast.  (Windows, r^
-        // on its slab and the shared finalizes: 32^3 x 64, 48 RHS FP16N 789 -> 700 ms; 16^3 x 32,
-        // 160 RHS 153 -> 144 ms)
+        // on its slab and the shared finalizes: 32^3 x 64, 48 RHS FP16N 790 -> 702 ms; 16^3 x 32,
+        // 160 RHS 156 -> 146 ms)
         int grow = 0;
         if (confined && (size_t)c->g.vh * ncur >= ((size_t)1 << 20))
             while (2 * (4 * (grow + 1) - 2) + 1 < c->g.lt) ++grow;
